@@ -67,7 +67,6 @@ __device__ __forceinline__ void tile_uncovered(const FramePlan &P, const TileGeo
   const int trow = tile / G.tiles_x;
   const int x0 = (tile - trow * G.tiles_x) * TW, y0 = trow * TH;
   const int ty = threadIdx.x >> lg, xr = x0 + (threadIdx.x & ((1 << lg) - 1)) * kRun;
-  const bool vec = vector_stores_ok(P, G);
   const float miss = G.nan_outside ? __builtin_nanf("") : 0.0f;
   float zo[kRun], zf[kRun];
 #pragma unroll
@@ -80,8 +79,8 @@ __device__ __forceinline__ void tile_uncovered(const FramePlan &P, const TileGeo
     const int y = y0 + ty + k * RP;
     if (y >= G.out_h || xr >= G.out_w) continue;
     const int64_t off = (int64_t)y * G.out_w + xr;
-    store_run(P.out, off, xr, G.out_w, vec, zo);
-    if (P.fp) store_run(P.fp, off, xr, G.out_w, vec, zf);
+    store_run(P.out, off, xr, G.out_w, zo);
+    if (P.fp) store_run(P.fp, off, xr, G.out_w, zf);
   }
 }
 
@@ -126,11 +125,11 @@ struct StoreSink {
   // run k of the thread (output row y, columns xr ..); `full`: every
   // footprint is exactly 1
   __device__ __forceinline__ void row(const FramePlan &P, const TileGeom &G, int k, int y,
-                                      int xr, bool vec, bool full, const float o[kRun],
+                                      int xr, bool full, const float o[kRun],
                                       const float f[kRun]) {
     const int64_t off = (int64_t)y * G.out_w + xr;
-    store_run(P.out, off, xr, G.out_w, vec, o);
-    if (P.fp) store_run(P.fp, off, xr, G.out_w, vec, f);
+    store_run(P.out, off, xr, G.out_w, o);
+    if (P.fp) store_run(P.fp, off, xr, G.out_w, f);
   }
 };
 
@@ -141,7 +140,7 @@ struct StackSink {
   float w[NP][kRun];  // sum of F
   template <int NP_>
   __device__ __forceinline__ void uncovered(const FramePlan &, const TileGeom &, int) {}
-  __device__ __forceinline__ void row(const FramePlan &, const TileGeom &, int k, int, int, bool,
+  __device__ __forceinline__ void row(const FramePlan &, const TileGeom &, int k, int, int,
                                       bool full, const float o[kRun], const float f[kRun]) {
 #pragma unroll
     for (int e = 0; e < kRun; ++e) {
@@ -172,17 +171,14 @@ struct CropSink {
   template <int NP>
   __device__ __forceinline__ void uncovered(const FramePlan &P, const TileGeom &G, int tile);
   __device__ __forceinline__ void row(const FramePlan &P, const TileGeom &G, int, int y, int xr,
-                                      bool, bool, const float o[kRun], const float f[kRun]) {
+                                      bool, const float o[kRun], const float f[kRun]) {
     const int cx = P.crop[0], cy = P.crop[1], cw = P.crop[2], ch = P.crop[3];
     if (y < cy || y >= cy + ch || xr + kRun <= cx || xr >= cx + cw) return;
     const int rx = xr - cx;
     const int64_t off = (int64_t)(y - cy) * cw + rx;
-    const bool vec = rx >= 0 && rx + kRun <= cw && ((rx | cw) & (kRun - 1)) == 0 &&
-                     ((reinterpret_cast<uintptr_t>(P.out) & 15) == 0) &&
-                     (P.fp == nullptr || (reinterpret_cast<uintptr_t>(P.fp) & 15) == 0);
-    if (vec) {
-      store_run(P.out, off, 0, kRun, true, o);
-      if (P.fp) store_run(P.fp, off, 0, kRun, true, f);
+    if (rx >= 0 && rx + kRun <= cw) {
+      store_run(P.out, off, 0, kRun, o);
+      if (P.fp) store_run(P.fp, off, 0, kRun, f);
       return;
     }
 #pragma unroll
@@ -493,7 +489,6 @@ __device__ __forceinline__ void tile_gather(const FramePlan &P, const TileGeom &
   constexpr int SPAN = TapSupport<INTERP>::lo + TapSupport<INTERP>::hi;
   const int W = P.src_w, Hs = P.src_h;
   const int xr = T.xr, lp = B.lp;
-  const bool vec = vector_stores_ok(P, G);
   const float miss = G.nan_outside ? __builtin_nanf("") : 0.0f;
   // Interior tiles need no per-pixel check: the box holds every tap by the
   // rigorous margin of the cells' models.
@@ -527,7 +522,7 @@ __device__ __forceinline__ void tile_gather(const FramePlan &P, const TileGeom &
         }
         f[e] = 1.0f;
       }
-      sink.row(P, G, k, y, xr, vec, true, o, f);
+      sink.row(P, G, k, y, xr, true, o, f);
     }
     return;
   }
@@ -563,7 +558,7 @@ __device__ __forceinline__ void tile_gather(const FramePlan &P, const TileGeom &
         }
       }
     }
-    sink.row(P, G, k, y, xr, vec, false, o, f);
+    sink.row(P, G, k, y, xr, false, o, f);
   }
 }
 
@@ -580,7 +575,7 @@ __device__ __forceinline__ void CropSink::uncovered(const FramePlan &P, const Ti
     zf[e] = 0.0f;
   }
 #pragma unroll
-  for (int k = 0; k < NP; ++k) row(P, G, k, T.y0 + T.ty + k * T.RP, T.xr, false, false, zo, zf);
+  for (int k = 0; k < NP; ++k) row(P, G, k, T.y0 + T.ty + k * T.RP, T.xr, false, zo, zf);
 }
 
 // Nearest, after the gather: the pixels flagged in `tie` (bit k * kRun + e

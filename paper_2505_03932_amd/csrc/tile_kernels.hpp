@@ -155,22 +155,19 @@ void coadd_tiles(const FramePlan *__restrict__ plans, int n_frames, TileGeom G, 
     forward_tile<INTERP, SORD, NP>(P, G, tile, lds, sh, acc);
     __syncthreads();  // LDS and the per-tile state are reused by the next frame
   }
-  const bool vec = ((G.out_w & (kRun - 1)) == 0) &&
-                   (((reinterpret_cast<uintptr_t>(C.sum_wf) | reinterpret_cast<uintptr_t>(C.sum_f) |
-                      reinterpret_cast<uintptr_t>(C.coadd)) & 15) == 0);
   const float miss = G.nan_outside ? __builtin_nanf("") : 0.0f;
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
     const int y = y0 + ty + k * RP;
     if (y >= G.out_h || xr >= G.out_w) continue;
     const int64_t off = (int64_t)y * G.out_w + xr;
-    store_run(C.sum_wf, off, xr, G.out_w, vec, acc.s[k]);
-    store_run(C.sum_f, off, xr, G.out_w, vec, acc.w[k]);
+    store_run(C.sum_wf, off, xr, G.out_w, acc.s[k]);
+    store_run(C.sum_f, off, xr, G.out_w, acc.w[k]);
     if (C.coadd) {
       float q[kRun];
 #pragma unroll
       for (int e = 0; e < kRun; ++e) q[e] = acc.w[k][e] > 0.0f ? acc.s[k][e] / acc.w[k][e] : miss;
-      store_run(C.coadd, off, xr, G.out_w, vec, q);
+      store_run(C.coadd, off, xr, G.out_w, q);
     }
   }
 }

@@ -1,0 +1,53 @@
+"""Output rows at every alignment: runs of four pixels are stored with one
+16-byte store whatever the row's address, the last run of a row pixel by
+pixel.  A width's results must equal, bit for bit, the left part of a wider
+16-byte aligned output on the same grid, and nothing may be written beside them."""
+import pytest
+import torch
+
+from synth import configs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dfr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_03932_amd as d
+    return d
+
+
+def _guarded(h, w, offset):
+    """A [h, w] view `offset` floats into a buffer of guard values."""
+    buf = torch.full((h * w + offset + 64,), -12345.0, device="cuda")
+    return buf, buf[offset:offset + h * w].view(h, w)
+
+
+@pytest.mark.parametrize("interp", ["nearest", "bilinear", "bicubic"])
+@pytest.mark.parametrize("width", [1, 2, 3, 5, 31, 126, 127, 129, 131, 200])
+def test_any_row_alignment(dfr, interp, width):
+    c = configs.plain()
+    src = torch.from_numpy(c.src).cuda()
+    h, wide = 67, 256
+    want, want_fp = dfr.reproject(src, c.src_wcs, c.tgt_wcs, (h, wide), interp)
+    for offset in (0, 1, 2, 3):
+        print(f"store runs interp={interp} width={width} offset={offset}", flush=True)
+        buf, out = _guarded(h, width, offset)
+        fbuf, fp = _guarded(h, width, (offset + 1) % 4)
+        dfr.reproject(src, c.src_wcs, c.tgt_wcs, (h, width), interp, out=out, fp=fp)
+        assert torch.equal(out, want[:, :width]) and torch.equal(fp, want_fp[:, :width])
+        for b, o in ((buf, offset), (fbuf, (offset + 1) % 4)):
+            assert (b[:o] == -12345.0).all() and (b[o + h * width:] == -12345.0).all()
+
+
+@pytest.mark.parametrize("x0,w", [(1, 61), (2, 64), (3, 5), (64, 63), (127, 2)])
+def test_window_at_any_column(dfr, x0, w):
+    c = configs.plain()
+    src = torch.from_numpy(c.src).cuda()
+    print(f"window x0={x0} w={w}", flush=True)
+    full, full_fp = dfr.reproject(src, c.src_wcs, c.tgt_wcs, (256, 256), "bilinear")
+    outs, fps, _ = dfr.reproject_batch_cropped([src], [c.src_wcs], c.tgt_wcs, (256, 256), "bilinear",
+                                               boxes=[[x0, 3, w, 70]])
+    assert torch.equal(outs[0], full[3:73, x0:x0 + w])
+    assert torch.equal(fps[0], full_fp[3:73, x0:x0 + w])
