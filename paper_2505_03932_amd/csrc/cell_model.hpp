@@ -48,10 +48,19 @@ __host__ __device__ constexpr int cm_idx(int i, int j) {
 }
 
 // Taylor model: degree-3 polynomial in (a, b) plus a bound r on the rest.
+// The functions below are told at compile time which degrees of their
+// arguments can be non-zero (LO .. HI: a linear form is <1, 1>, a quantity
+// without a constant term <1, 3>) and leave out the products and norms of the
+// others: without that the compiler, which may not drop a multiplication by
+// zero, keeps all of them.  The terms that remain are combined in the same
+// order, so the result has the same bits (order 4: 718 FP64 instructions per
+// lane instead of 988; the models of a 6000x4000 grid 5.5 us instead of 6.0).
 struct Tm3 {
   double c[10];
   double r;
 };
+
+__host__ __device__ constexpr int cm_deg(int k) { return cm_i(k) + cm_j(k); }
 
 __host__ __device__ inline void tm_zero(Tm3 &t) {
 #pragma unroll
@@ -60,23 +69,30 @@ __host__ __device__ inline void tm_zero(Tm3 &t) {
 }
 
 // Sum of |c| h^d over the terms of each degree d.
+template <int LO, int HI>
 __host__ __device__ inline void tm_norms(const Tm3 &t, double n[4]) {
   const double h = kHalfCell;
   const double hp[4] = {1.0, h, h * h, h * h * h};
 #pragma unroll
   for (int d = 0; d < 4; ++d) n[d] = 0.0;
 #pragma unroll
-  for (int k = 0; k < 10; ++k) n[cm_i(k) + cm_j(k)] += __builtin_fabs(t.c[k]) * hp[cm_i(k) + cm_j(k)];
+  for (int k = 0; k < 10; ++k)
+    if (cm_deg(k) >= LO && cm_deg(k) <= HI) n[cm_deg(k)] += __builtin_fabs(t.c[k]) * hp[cm_deg(k)];
 }
 
 // Bound on |t| over the cell.
+template <int LO, int HI>
 __host__ __device__ inline double tm_bound(const Tm3 &t) {
-  double n[4];
-  tm_norms(t, n);
-  return n[0] + n[1] + n[2] + n[3] + t.r;
+  double n[4], b = t.r;
+  tm_norms<LO, HI>(t, n);
+  double s = 0.0;
+#pragma unroll
+  for (int d = LO; d <= HI; ++d) s += n[d];
+  return s + b;
 }
 
 // z = x * y: product terms of degree <= 3 kept, the others bounded.
+template <int XLO, int XHI, int YLO, int YHI>
 __host__ __device__ inline void tm_mul(const Tm3 &x, const Tm3 &y, Tm3 &z) {
 #pragma unroll
   for (int k = 0; k < 10; ++k) z.c[k] = 0.0;
@@ -84,26 +100,33 @@ __host__ __device__ inline void tm_mul(const Tm3 &x, const Tm3 &y, Tm3 &z) {
   for (int kx = 0; kx < 10; ++kx)
 #pragma unroll
     for (int ky = 0; ky < 10; ++ky) {
-      const int i = cm_i(kx) + cm_i(ky), j = cm_j(kx) + cm_j(ky);
-      if (i + j <= 3) z.c[cm_idx(i, j)] = __builtin_fma(x.c[kx], y.c[ky], z.c[cm_idx(i, j)]);
+      const int dx = cm_deg(kx), dy = cm_deg(ky);
+      if (dx < XLO || dx > XHI || dy < YLO || dy > YHI || dx + dy > 3) continue;
+      double &t = z.c[cm_idx(cm_i(kx) + cm_i(ky), cm_j(kx) + cm_j(ky))];
+      t = __builtin_fma(x.c[kx], y.c[ky], t);
     }
   double nx[4], ny[4];
-  tm_norms(x, nx);
-  tm_norms(y, ny);
-  double drop = 0.0;
+  tm_norms<XLO, XHI>(x, nx);
+  tm_norms<YLO, YHI>(y, ny);
+  double drop = 0.0, bx = 0.0, by = 0.0;
 #pragma unroll
-  for (int d1 = 0; d1 < 4; ++d1)
+  for (int d1 = XLO; d1 <= XHI; ++d1)
 #pragma unroll
-    for (int d2 = 0; d2 < 4; ++d2)
+    for (int d2 = YLO; d2 <= YHI; ++d2)
       if (d1 + d2 >= 4) drop += nx[d1] * ny[d2];
-  const double bx = nx[0] + nx[1] + nx[2] + nx[3], by = ny[0] + ny[1] + ny[2] + ny[3];
+#pragma unroll
+  for (int d = XLO; d <= XHI; ++d) bx += nx[d];
+#pragma unroll
+  for (int d = YLO; d <= YHI; ++d) by += ny[d];
   z.r = drop + bx * y.r + by * x.r + x.r * y.r;
 }
 
 // z += s * x
+template <int LO, int HI>
 __host__ __device__ inline void tm_axpy(double s, const Tm3 &x, Tm3 &z) {
 #pragma unroll
-  for (int k = 0; k < 10; ++k) z.c[k] = __builtin_fma(s, x.c[k], z.c[k]);
+  for (int k = 0; k < 10; ++k)
+    if (cm_deg(k) >= LO && cm_deg(k) <= HI) z.c[k] = __builtin_fma(s, x.c[k], z.c[k]);
   z.r += __builtin_fabs(s) * x.r;
 }
 
@@ -176,11 +199,11 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   tm_zero(eps);
   eps.c[cm_idx(1, 0)] = k1;
   eps.c[cm_idx(0, 1)] = k2;
-  tm_mul(eps, eps, e2);
-  tm_mul(e2, eps, e3);
+  tm_mul<1, 1, 1, 1>(eps, eps, e2);
+  tm_mul<2, 2, 1, 1>(e2, eps, e3);
 #pragma unroll
-  for (int k = 0; k < 10; ++k) rho.c[k] = e2.c[k] - eps.c[k] - e3.c[k];
-  rho.c[0] += 1.0;
+  for (int k = 0; k < 10; ++k)
+    rho.c[k] = cm_deg(k) == 0 ? 1.0 : (cm_deg(k) == 1 ? -eps.c[k] : (cm_deg(k) == 2 ? e2.c[k] : -e3.c[k]));
   rho.r = kap * kap * kap * kap / (1.0 - kap);
 
   Tm3 gd, fd, al, be;
@@ -190,8 +213,8 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   gd.c[cm_idx(0, 1)] = g2;
   fd.c[cm_idx(1, 0)] = f1;
   fd.c[cm_idx(0, 1)] = f2;
-  tm_mul(gd, rho, al);  // dU
-  tm_mul(fd, rho, be);  // dV
+  tm_mul<1, 1, 0, 3>(gd, rho, al);  // dU
+  tm_mul<1, 1, 0, 3>(fd, rho, be);  // dV
 
   Tm3 X = al, Y = be;
   double sa0 = 0.0, sb0 = 0.0;
@@ -202,35 +225,35 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
     sa0 = ta[0];
     sb0 = tb[0];
     // degree 1..3 in (dU, dV): Taylor-model powers of al, be
-    tm_axpy(ta[tri9(1, 0)], al, X);
-    tm_axpy(ta[tri9(0, 1)], be, X);
-    tm_axpy(tb[tri9(1, 0)], al, Y);
-    tm_axpy(tb[tri9(0, 1)], be, Y);
+    tm_axpy<1, 3>(ta[tri9(1, 0)], al, X);
+    tm_axpy<1, 3>(ta[tri9(0, 1)], be, X);
+    tm_axpy<1, 3>(tb[tri9(1, 0)], al, Y);
+    tm_axpy<1, 3>(tb[tri9(0, 1)], be, Y);
     if (N >= 2) {
       Tm3 p2[3];  // al^2, al be, be^2
-      tm_mul(al, al, p2[0]);
-      tm_mul(al, be, p2[1]);
-      tm_mul(be, be, p2[2]);
+      tm_mul<1, 3, 1, 3>(al, al, p2[0]);
+      tm_mul<1, 3, 1, 3>(al, be, p2[1]);
+      tm_mul<1, 3, 1, 3>(be, be, p2[2]);
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        tm_axpy(ta[tri9(2 - i, i)], p2[i], X);
-        tm_axpy(tb[tri9(2 - i, i)], p2[i], Y);
+        tm_axpy<2, 3>(ta[tri9(2 - i, i)], p2[i], X);
+        tm_axpy<2, 3>(tb[tri9(2 - i, i)], p2[i], Y);
       }
       if (N >= 3) {
         Tm3 p3;  // al^(3-i) be^i
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (i == 0)
-            tm_mul(p2[0], al, p3);
+            tm_mul<2, 3, 1, 3>(p2[0], al, p3);
           else
-            tm_mul(p2[i - 1], be, p3);
-          tm_axpy(ta[tri9(3 - i, i)], p3, X);
-          tm_axpy(tb[tri9(3 - i, i)], p3, Y);
+            tm_mul<2, 3, 1, 3>(p2[i - 1], be, p3);
+          tm_axpy<3, 3>(ta[tri9(3 - i, i)], p3, X);
+          tm_axpy<3, 3>(tb[tri9(3 - i, i)], p3, Y);
         }
       }
     }
     // degree >= 4 in (dU, dV): bounded term by term
-    const double A = tm_bound(al), B = tm_bound(be);
+    const double A = tm_bound<1, 3>(al), B = tm_bound<1, 3>(be);
     double apow[N + 1], bpow[N + 1];
     apow[0] = bpow[0] = 1.0;
 #pragma unroll
@@ -271,7 +294,7 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
     }
   }
   // FP64 rounding of this construction, generously
-  const double slack = 1.0e-12 * (1.0 + __builtin_fabs(Uc) + __builtin_fabs(Vc) + tm_bound(al) + tm_bound(be));
+  const double slack = 1.0e-12 * (1.0 + __builtin_fabs(Uc) + __builtin_fabs(Vc) + tm_bound<1, 3>(al) + tm_bound<1, 3>(be));
   const double tx = X.r + slack, ty = Y.r + slack;  // truncation of the map
   const double errx = tx + rx, erry = ty + ry;       // plus FP32 rounding of the coefficients
   const double err = __builtin_fmax(errx, erry);

@@ -379,7 +379,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   const int64_t nzero = 4 + 4 * (int64_t)n;  // counter padded to 16 bytes, then the boxes
   const size_t tofs = ((size_t)nzero * 4 + 255) & ~(size_t)255;
   const size_t mofs = (tofs + table + 255) & ~(size_t)255;
-  const size_t mbytes = models ? (size_t)n * ncells * sizeof(CellModel) : 0;
+  const size_t mbytes = models && !run.reach_host ? (size_t)n * ncells * sizeof(CellModel) : 0;
   void *wsbuf = nullptr;
   dfr_status ws = workspace_buffer(w, mofs + mbytes, &wsbuf);
   if (ws != DFR_OK) return ws;
@@ -387,7 +387,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   int *counter = reinterpret_cast<int *>(dev);
   int32_t *reach = reinterpret_cast<int32_t *>(dev) + 4;
   FramePlan *plans_dev = reinterpret_cast<FramePlan *>(dev + tofs);
-  CellModel *models_dev = models ? reinterpret_cast<CellModel *>(dev + mofs) : nullptr;
+  CellModel *models_dev = mbytes ? reinterpret_cast<CellModel *>(dev + mofs) : nullptr;
   // the previous batch on this stream must have copied the staged table
   if (w->staged_pending) {
     if (hipEventSynchronize(w->staged) != hipSuccess) return DFR_E_DEVICE;
@@ -404,7 +404,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   }
   std::memcpy(w->host_plans, plans.data(), table);
   for (int i = 0; i < n; ++i) {
-    w->host_plans[i].models = models ? models_dev + i * ncells : nullptr;
+    w->host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
     w->host_plans[i].reach = models ? reach + 4 * i : nullptr;
   }
   int dev_id = 0, cus = 0;
@@ -414,23 +414,22 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
     cus = 1;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
   const int grid = batch_blocks_per_cu(interp, np, max_sord, lds_bytes) * cus;
-  const int64_t mtotal = (int64_t)n * ncells;
-  const dim3 mgrid((unsigned)((mtotal + 63) / 64));
-  int ncx_i = ncx, ncells_i = (int)ncells;
-  int64_t mtotal_i = mtotal;
-  void *margs[] = {&plans_dev, &ncx_i, &ncells_i, &mtotal_i, &models_dev};
+  int ncx_i = ncx, ncells_i = (int)ncells, bpf = (int)((ncells + 63) / 64);
+  const dim3 mgrid((unsigned)n * (unsigned)bpf);
+  const void *mkernel = cell_models_batch_ptr(max_sord);
+  void *margs[] = {&plans_dev, &ncx_i, &ncells_i, &bpf, &models_dev};
   if (!graph) {
     if (hipMemcpyAsync(plans_dev, w->host_plans, table, hipMemcpyHostToDevice, stream) !=
         hipSuccess)
       return DFR_E_DEVICE;
     // counter and reach boxes start at zero; the prepass then records the boxes
     if (launch_zero_i32(counter, nzero, stream) != hipSuccess) return DFR_E_DEVICE;
-    if (models && hipLaunchKernel(cell_models_batch_ptr(max_sord), mgrid, dim3(64), margs, 0,
-                                  stream) != hipSuccess)
+    if (models &&
+        hipLaunchKernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
     if (run.reach_host) {
-      // the reach boxes the prepass recorded, back to the host (no model
-      // table: every frame may reach everywhere, reported as -1); the wait
+      // the reach boxes the prepass recorded, back to the host (none:
+      // every frame may reach everywhere, reported as -1); the wait
       // also ends the frame table's copy from the pinned staging buffer,
       // which the next batch on this stream refills
       if (models && hipMemcpyAsync(run.reach_host, reach, (size_t)16 * n, hipMemcpyDeviceToHost,
@@ -452,7 +451,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
     BatchGraph *found = nullptr;
     for (auto &g : w->graphs)
       if (g.n == n && g.interp == interp && g.np == np && g.sord == max_sord && g.grid == grid &&
-          g.models == (int)models && g.plans_dev == plans_dev && g.plans_host == w->host_plans &&
+          g.models == (models ? mkernel : nullptr) && g.plans_dev == plans_dev && g.plans_host == w->host_plans &&
           std::memcmp(&g.geom, &G, sizeof(G)) == 0)
         found = &g;
     if (!found) {
@@ -464,7 +463,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       bg.np = np;
       bg.sord = max_sord;
       bg.grid = grid;
-      bg.models = (int)models;
+      bg.models = models ? mkernel : nullptr;
       bg.plans_dev = plans_dev;
       bg.plans_host = w->host_plans;
       if (hipGraphCreate(&bg.graph, 0) != hipSuccess) return DFR_E_DEVICE;
@@ -474,7 +473,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       if (models) {
         hipKernelNodeParams mp;
         std::memset(&mp, 0, sizeof(mp));
-        mp.func = const_cast<void *>(cell_models_batch_ptr(max_sord));
+        mp.func = const_cast<void *>(mkernel);
         mp.gridDim = mgrid;
         mp.blockDim = dim3(64);
         mp.sharedMemBytes = 0;

@@ -55,7 +55,8 @@ void make_geom(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int
 // here must be called with workspace_mutex() held.
 struct BatchGraph {
   TileGeom geom;
-  int n, interp, np, sord, grid, models;
+  int n, interp, np, sord, grid;
+  const void *models;  // the model prepass kernel, null without one
   void *plans_dev;
   void *plans_host;
   hipGraph_t graph;
