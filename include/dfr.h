@@ -83,8 +83,8 @@ typedef enum {
 typedef enum {
   DFR_PREC_F32 = 0,      /* FP64 set-up per 32x32 cell, FP32 per pixel (default): a
                             certified cubic model of the cell's position map where
-                            its bound holds (target without SIP), else the full
-                            chain as FP32 offsets from an FP64 anchor              */
+                            its bound holds, else the full chain as FP32 offsets
+                            from an FP64 anchor                                    */
   DFR_PREC_F64 = 1,      /* every pixel in FP64 through the composed rotation        */
   DFR_PREC_TRIG_F64 = 2, /* every pixel in FP64 through explicit (RA, Dec) and the
                             trigonometric two-stage form of section 3.2              */
@@ -139,7 +139,10 @@ dfr_status dfr_reproject(const float *src, int32_t src_h, int32_t src_w, int64_t
  *   Limit: with the default precision (DFR_PREC_F32) and a target without
  *   SIP the table takes 112 B per 32x32 output cell, so at most 74,898 cells
  *   (e.g. 8192 x 8192); a larger output returns DFR_E_LIMIT before any
- *   device work.  The other precisions use no scratch and have no limit.
+ *   device work.  The other precisions use no scratch and have no limit;
+ *   nor does a target with SIP, whose pixels all take the chain from anchors
+ *   here (the results of DFR_PREC_F32_ANCHOR, within 2e-5 px of those of
+ *   dfr_reproject, which models such a target's cells too).
  *   Sharing: every call on one GPU uses that GPU's one array.  Calls whose
  *   device work can overlap (different streams without ordering, several
  *   host threads) race on it and give wrong results; calls ordered on one
@@ -211,8 +214,8 @@ dfr_status dfr_reproject_batch(int32_t n, const dfr_frame *frames, const dfr_wcs
  * clipped to the output; w = h = 0 when no pixel can reach the frame).
  * Every pixel outside frame i's box is uncovered in dfr_reproject_batch
  * (the boxes come from the rigorous bounds of the model prepass, which this
- * runs on `stream` and waits for; with a target SIP there are no models and
- * every box is the whole grid).  Errors as for dfr_reproject_batch. */
+ * runs on `stream` and waits for; with a target SIP every box is the whole
+ * grid).  Errors as for dfr_reproject_batch. */
 dfr_status dfr_batch_boxes(int32_t n, const dfr_frame *frames, const dfr_wcs *tgt_wcs,
                            int32_t out_h, int32_t out_w, dfr_interp interp,
                            const dfr_options *opt, void *stream, int32_t *boxes);
@@ -314,7 +317,8 @@ dfr_status dfr_check_wcs(const dfr_wcs *wcs, int32_t as_source);
  * with (i, j) for k = 0..9: (0,0) (0,1) (0,2) (0,3) (1,0) (1,1) (1,2) (2,0)
  * (2,1) (3,0); the coefficients are the FP32 values the kernels use.
  * `bound` receives a rigorous bound (px) on |model - exact position| over the
- * whole cell (1e30 where no model exists: a target with SIP, a projective
+ * whole cell (1e30 where this host form has none: a target with SIP, whose
+ * models are made on the device, a projective
  * denominator that may vanish in the cell), `certified` 1 when the kernels
  * use the model: the part of the bound the cubic leaves out of the map is
  * <= 1e-6 px (the rest is the FP32 rounding of the coefficients, about

@@ -39,16 +39,26 @@ bool is_f32(const dfr_options &o) {
 }
 
 // FP32 forward of one frame with tile `tile`: the per-cell position models
-// first where the map allows them (default precision, target without SIP;
-// the table lives in the stream's workspace, so the caller holds
-// workspace_mutex() from here until every launch reading it is queued).
+// first (default precision; the table lives in the stream's workspace, so the
+// caller holds workspace_mutex() from here until every launch reading it is
+// queued).  A target with SIP does without the table (the anchored chain)
+// where it cannot be had: no memory, or a stream being captured, where the
+// workspace cannot grow.
 dfr_status models_for(FramePlan &P, int32_t out_h, int32_t out_w, const dfr_options &o,
                       hipStream_t st) {
   P.models = nullptr;
-  if (o.precision != DFR_PREC_F32 || P.t_order > 0) return DFR_OK;
+  if (o.precision != DFR_PREC_F32) return DFR_OK;
   const int ncx = (out_w + kCell - 1) / kCell, ncy = (out_h + kCell - 1) / kCell;
+  const size_t bytes = (size_t)ncx * ncy * sizeof(CellModel);
+  Workspace *w = workspace(st);
+  if (P.t_order > 0 && w && w->cap < bytes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) return DFR_E_DEVICE;
+    if (cap != hipStreamCaptureStatusNone) return DFR_OK;
+  }
   void *buf = nullptr;
-  dfr_status s = workspace_buffer(workspace(st), (size_t)ncx * ncy * sizeof(CellModel), &buf);
+  dfr_status s = workspace_buffer(w, bytes, &buf);
+  if (s == DFR_E_NOMEM && P.t_order > 0) return DFR_OK;
   if (s != DFR_OK) return s;
   CellModel *table = static_cast<CellModel *>(buf);
   P.models = table;
@@ -267,6 +277,8 @@ dfr_status dfr_reproject_noalloc(const float *src, int32_t src_h, int32_t src_w,
     single_setup(src, src_h, src_w, src_pitch, *src_wcs, *tgt_wcs, out_h, out_w, out, footprint,
                  (int)interp, o, P, G, ts);
     P.models = nullptr;
+    // (a target with SIP takes the anchored chain here: its calls need no
+    // scratch, so they have no limit and may overlap)
     if (o.precision == DFR_PREC_F32 && P.t_order == 0) {
       // the model table goes to the device's fixed scratch, not the
       // stream's workspace: refuse a grid whose table does not fit before
@@ -464,16 +476,19 @@ dfr_status dfr_plan_create(int32_t src_h, int32_t src_w, const dfr_wcs *src_wcs,
   const int tile = choose_tile(pl->P, out_h, out_w, (int)interp, o.tile, false);
   make_geom(pl->P, out_h, out_w, (int)interp, tile, o, pl->G, ts);
   pl->np = ts.np;
-  if (o.precision == DFR_PREC_F32 && pl->P.t_order == 0 && out_h > 0 && out_w > 0) {
+  if (o.precision == DFR_PREC_F32 && out_h > 0 && out_w > 0) {
     const int ncx = (out_w + kCell - 1) / kCell, ncy = (out_h + kCell - 1) / kCell;
     if (hipMalloc(&pl->models, (size_t)ncx * ncy * sizeof(CellModel)) != hipSuccess) {
       pl->models = nullptr;
-      delete pl;
-      return DFR_E_NOMEM;
+      if (pl->P.t_order == 0) {
+        delete pl;
+        return DFR_E_NOMEM;
+      }
+      (void)hipGetLastError();  // a target with SIP does without: the anchored chain
     }
     pl->P.models = pl->models;
-    if (launch_cell_models(pl->P, ncx, ncy, pl->models, reinterpret_cast<hipStream_t>(stream)) !=
-        hipSuccess) {
+    if (pl->models && launch_cell_models(pl->P, ncx, ncy, pl->models,
+                                         reinterpret_cast<hipStream_t>(stream)) != hipSuccess) {
       (void)hipFree(pl->models);
       delete pl;
       return DFR_E_DEVICE;
@@ -742,7 +757,7 @@ dfr_status dfr_cell_model(const dfr_wcs *src_wcs, const dfr_wcs *tgt_wcs, int32_
   build_plan(nullptr, 0, 0, 0, *src_wcs, *tgt_wcs, (cy + 1) * kCell, (cx + 1) * kCell, nullptr,
              nullptr, P);
   CellModel M;
-  cell_model<-1>(P, cx, cy, M);
+  cell_model<-1>(P, cx, cy, M);  // (the models of a target with SIP exist on the device only)
   for (int k = 0; k < 10; ++k) {
     if (coef_x) coef_x[k] = M.mx[k];
     if (coef_y) coef_y[k] = M.my[k];

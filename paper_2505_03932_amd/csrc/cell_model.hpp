@@ -1,5 +1,4 @@
-// Certified local models of the position map (forward path, target
-// without SIP).
+// Certified local models of the position map (forward path).
 //
 // For a 32x32 cell of output pixels with centre (xc, yc), the source
 // position of pixel (xc + a, yc + b), |a|, |b| <= 15.5, is written as
@@ -8,7 +7,9 @@
 // from Taylor-model arithmetic in FP64 (a degree-3 polynomial in (a, b) and
 // an interval for everything it leaves out) applied to the two stages of
 // section 3.2 in their composed form:
-//   1. the projective step: dU = (g.d) / (1 + e), e = k.d linear in (a, b);
+//   0. a target with SIP: its A/B re-expanded about the cell centre give the
+//      corrected target offset d as a Taylor model (d = (a, b) without SIP);
+//   1. the projective step: dU = (g.d) / (1 + e), e = k.d;
 //      1/(1 + e) = 1 - e + e^2 - e^3 + e^4/(1 + e), |e| <= kap < 1/4;
 //   2. the source SIP AP/BP re-expanded about the cell centre's (U, V)
 //      (Taylor shift of the polynomial: exact up to rounding) and composed
@@ -162,8 +163,9 @@ __host__ __device__ inline void sip_taylor(const double *__restrict__ c, double 
 
 // Position model of cell (cx, cy) of the output grid.  SORD: source SIP
 // order at compile time (< 0: any order up to kMaxOrder; the padded
-// coefficients make both give the same model).
-template <int SORD>
+// coefficients make both give the same model).  TN: highest target SIP order
+// the instance covers (0: a target with SIP gets no model).
+template <int SORD, int TN = 0>
 __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, CellModel &M) {
   constexpr int N = SORD >= 0 ? SORD : kMaxOrder;
   const double h = kHalfCell;
@@ -178,9 +180,36 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   M.certified = 0;
   M.tie = 0.5f;
   M.pad_ = 0;
-  if (P.t_order > 0) return;  // the target SIP is not modelled
+  if (P.t_order > TN) return;
 
-  const double uc = (double)cx * kCell + h - P.tcr[0], vc = (double)cy * kCell + h - P.tcr[1];
+  double uc = (double)cx * kCell + h - P.tcr[0], vc = (double)cy * kCell + h - P.tcr[1];
+  Tm3 du, dv;  // SIP-corrected target offset from the centre's
+  if constexpr (TN > 0) {
+    double t[kMaxCoef];
+    auto correct = [&](const double *c, int main, Tm3 &d) {
+      sip_taylor<TN>(c, uc, vc, t);
+      tm_zero(d);
+      double hp[TN + 1];
+      hp[0] = 1.0;
+#pragma unroll
+      for (int i = 1; i <= TN; ++i) hp[i] = hp[i - 1] * h;
+#pragma unroll
+      for (int i = 0; i <= TN; ++i)
+#pragma unroll
+        for (int j = 0; i + j <= TN; ++j) {
+          if (i + j == 0) continue;
+          if (i + j <= 3)
+            d.c[cm_idx(i, j)] = t[tri9(i, j)];
+          else
+            d.r += __builtin_fabs(t[tri9(i, j)]) * hp[i + j];
+        }
+      d.c[main] += 1.0;
+      return t[0];
+    };
+    const double a0 = correct(P.tA, cm_idx(1, 0), du), b0 = correct(P.tB, cm_idx(0, 1), dv);
+    uc += a0;
+    vc += b0;
+  }
   const double *H = P.H;
   const double pc = __builtin_fma(H[0], uc, __builtin_fma(H[1], vc, H[2]));
   const double qc = __builtin_fma(H[3], uc, __builtin_fma(H[4], vc, H[5]));
@@ -191,30 +220,48 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   const double g1 = (H[0] - Uc * H[6]) * iw, g2 = (H[1] - Uc * H[7]) * iw;
   const double f1 = (H[3] - Vc * H[6]) * iw, f2 = (H[4] - Vc * H[7]) * iw;
   const double k1 = H[6] * iw, k2 = H[7] * iw;
-  const double kap = (__builtin_fabs(k1) + __builtin_fabs(k2)) * h;
+
+  // e = k.d, g.d and f.d: linear in (a, b), or Taylor models with target SIP
+  constexpr int LH = TN > 0 ? 3 : 1;
+  auto dot = [&](double c1, double c2, Tm3 &z) {
+    tm_zero(z);
+    if constexpr (TN > 0) {
+      tm_axpy<1, 3>(c1, du, z);
+      tm_axpy<1, 3>(c2, dv, z);
+    } else {
+      z.c[cm_idx(1, 0)] = c1;
+      z.c[cm_idx(0, 1)] = c2;
+    }
+  };
+  Tm3 eps, e2, e3, rho;
+  dot(k1, k2, eps);
+  const double kap = TN > 0 ? tm_bound<1, LH>(eps) : (__builtin_fabs(k1) + __builtin_fabs(k2)) * h;
   if (!(kap < 0.25)) return;
 
   // 1 / (1 + e) as a Taylor model
-  Tm3 eps, e2, e3, rho;
-  tm_zero(eps);
-  eps.c[cm_idx(1, 0)] = k1;
-  eps.c[cm_idx(0, 1)] = k2;
-  tm_mul<1, 1, 1, 1>(eps, eps, e2);
-  tm_mul<2, 2, 1, 1>(e2, eps, e3);
+  constexpr int H2 = TN > 0 ? 3 : 2;  // e^2: degrees 2 .. H2
+  tm_mul<1, LH, 1, LH>(eps, eps, e2);
+  tm_mul<2, H2, 1, LH>(e2, eps, e3);
 #pragma unroll
-  for (int k = 0; k < 10; ++k)
-    rho.c[k] = cm_deg(k) == 0 ? 1.0 : (cm_deg(k) == 1 ? -eps.c[k] : (cm_deg(k) == 2 ? e2.c[k] : -e3.c[k]));
+  for (int k = 0; k < 10; ++k) {
+    const int d = cm_deg(k);
+    if (d == 0)
+      rho.c[k] = 1.0;
+    else if (d == 1)
+      rho.c[k] = -eps.c[k];
+    else if (d == 2)
+      rho.c[k] = TN > 0 ? e2.c[k] - eps.c[k] : e2.c[k];
+    else
+      rho.c[k] = TN > 0 ? e2.c[k] - eps.c[k] - e3.c[k] : -e3.c[k];
+  }
   rho.r = kap * kap * kap * kap / (1.0 - kap);
+  if constexpr (TN > 0) rho.r += eps.r + e2.r + e3.r;
 
   Tm3 gd, fd, al, be;
-  tm_zero(gd);
-  tm_zero(fd);
-  gd.c[cm_idx(1, 0)] = g1;
-  gd.c[cm_idx(0, 1)] = g2;
-  fd.c[cm_idx(1, 0)] = f1;
-  fd.c[cm_idx(0, 1)] = f2;
-  tm_mul<1, 1, 0, 3>(gd, rho, al);  // dU
-  tm_mul<1, 1, 0, 3>(fd, rho, be);  // dV
+  dot(g1, g2, gd);
+  dot(f1, f2, fd);
+  tm_mul<1, LH, 0, 3>(gd, rho, al);  // dU
+  tm_mul<1, LH, 0, 3>(fd, rho, be);  // dV
 
   Tm3 X = al, Y = be;
   double sa0 = 0.0, sb0 = 0.0;

@@ -29,14 +29,14 @@ hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp,
 
 // One lane per 32x32 cell of the output grid: the certified cubic model of
 // the cell's position map (cell_model.hpp), written to the model table.
-template <int SORD>
+template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, int n,
                                                         CellModel *__restrict__ out) {
   const int i = blockIdx.x * 64 + threadIdx.x;
   if (i >= n) return;
   const int cy = i / ncx, cx = i - cy * ncx;
   CellModel M;
-  cell_model<SORD>(P, cx, cy, M);
+  cell_model<SORD, TN>(P, cx, cy, M);
   out[i] = M;
 }
 
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, i
 // scalar loads; with cells numbered across frames the plan's address differed
 // per lane as far as the compiler knew, and every coefficient was a vector load
 // (64 frames on 8192^2, order 5: 397 us instead of 541 with the cheaper models).
-template <int SORD>
+template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *__restrict__ plans,
                                                               int ncx, int ncells, int bpf,
                                                               CellModel *__restrict__ out) {
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
   int reach = 0;
   if (c < ncells) {
     CellModel M;
-    cell_model<SORD>(P, cx, cy, M);
+    cell_model<SORD, TN>(P, cx, cy, M);
     if (out) out[(int64_t)frame * ncells + c] = M;  // null: only the reach boxes are wanted
     // can any pixel of the cell have a tap inside the source?  From the
     // model's range over the whole cell, grown by 4 px (more than any tap
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
       reach = 0;
     } else if (!M.certified) {
       Anchor A;
-      compute_anchor<SORD, false>(P, cx * kCell, cy * kCell, 4, A);
+      compute_anchor<SORD, (TN > 0)>(P, cx * kCell, cy * kCell, 4, A);
       reach = A.touch;
     } else {
       const float h = (float)kHalfCell;
@@ -94,29 +94,35 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
   }
 }
 
-template <template <int> class K>
-static const void *pick_models(int sord) {
+// Instances: source orders 0 .. 5 (and any) for a target without SIP; with
+// target SIP both orders up to 5, or any (padding with zero coefficients is
+// exact, and one instance keeps the library small).  A distorted 2048^2 target,
+// orders 3 and 4, bilinear: 128 us per call when every pixel took the chain
+// from anchors, 34 us with models (7.5 us of it this kernel).
+template <template <int, int> class K>
+static const void *pick_models(int sord, int tord) {
+  if (tord > 0) return sord >= 0 && sord <= 5 && tord <= 5 ? K<5, 5>::ptr() : K<-1, kMaxOrder>::ptr();
   switch (sord) {
-    case 0: return K<0>::ptr();
-    case 1: return K<1>::ptr();
-    case 2: return K<2>::ptr();
-    case 3: return K<3>::ptr();
-    case 4: return K<4>::ptr();
-    case 5: return K<5>::ptr();
-    default: return K<-1>::ptr();
+    case 0: return K<0, 0>::ptr();
+    case 1: return K<1, 0>::ptr();
+    case 2: return K<2, 0>::ptr();
+    case 3: return K<3, 0>::ptr();
+    case 4: return K<4, 0>::ptr();
+    case 5: return K<5, 0>::ptr();
+    default: return K<-1, 0>::ptr();
   }
 }
 
-template <int SORD>
+template <int SORD, int TN>
 struct ModelsK {
-  static const void *ptr() { return reinterpret_cast<const void *>(cell_models_kernel<SORD>); }
+  static const void *ptr() { return reinterpret_cast<const void *>(cell_models_kernel<SORD, TN>); }
 };
-template <int SORD>
+template <int SORD, int TN>
 struct ModelsBatchK {
-  static const void *ptr() { return reinterpret_cast<const void *>(cell_models_batch_kernel<SORD>); }
+  static const void *ptr() { return reinterpret_cast<const void *>(cell_models_batch_kernel<SORD, TN>); }
 };
 
-const void *cell_models_batch_ptr(int sord) { return pick_models<ModelsBatchK>(sord); }
+const void *cell_models_batch_ptr(int sord, int tord) { return pick_models<ModelsBatchK>(sord, tord); }
 
 hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *out,
                               hipStream_t stream) {
@@ -124,8 +130,8 @@ hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *o
   if (n <= 0) return hipSuccess;
   FramePlan plan = P;
   void *args[] = {&plan, &ncx, &n, &out};
-  return hipLaunchKernel(pick_models<ModelsK>(P.s_order), dim3((n + 63) / 64), dim3(64), args, 0,
-                         stream);
+  return hipLaunchKernel(pick_models<ModelsK>(P.s_order, P.t_order), dim3((n + 63) / 64), dim3(64),
+                         args, 0, stream);
 }
 
 // ------------------------------------------------------ FP64 comparison forms

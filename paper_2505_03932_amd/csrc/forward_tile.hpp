@@ -353,7 +353,8 @@ __device__ __forceinline__ TileBox tile_box(const FramePlan &P, const TileGeom &
   B.bh = box_ok ? B.bj1 - B.bj0 + 1 : 0;
   B.lp = lds_pitch(B.bw);  // padded row stride (bank spread)
   B.use_lds = box_ok && (int64_t)B.lp * B.bh <= (int64_t)lds_cap;
-  B.interior = B.use_lds && sh.cells_ok && P.t_order == 0 && bu0 == B.bi0 && bu1 == B.bi1 &&
+  // (an anchor's box does not bound the target SIP; a model's does)
+  B.interior = B.use_lds && sh.cells_ok && (P.t_order == 0 || sh.all_model) && bu0 == B.bi0 && bu1 == B.bi1 &&
                bu2 == B.bj0 && bu3 == B.bj1 && T.x0 + T.TW <= G.out_w && T.y0 + T.TH <= G.out_h;
   B.all_model = sh.all_model;
   B.touch = sh.touch;

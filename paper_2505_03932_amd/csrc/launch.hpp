@@ -55,8 +55,9 @@ hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp,
 hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *out,
                               hipStream_t stream);
 // Kernel (plans, ncx, ncells, bpf, out) modelling every cell of every frame
-// of a batch, bpf blocks of 64 threads per frame; sord as for the batch kernel.
-const void *cell_models_batch_ptr(int sord);
+// of a batch, bpf blocks of 64 threads per frame; sord as for the batch
+// kernel, tord the target SIP order.
+const void *cell_models_batch_ptr(int sord, int tord);
 hipError_t launch_forward_f64(const FramePlan &P, const TrigPlan &T, const TileGeom &G,
                               int interp, bool trig, hipStream_t stream);
 hipError_t launch_batch_f32(const FramePlan *plans_dev, int n_frames, int max_sord,

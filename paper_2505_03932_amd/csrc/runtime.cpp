@@ -373,15 +373,26 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   const size_t table = (size_t)n * sizeof(FramePlan);
   // counter + reach boxes (4 ints per frame, zeroed together) | frame table |
   // per-frame model tables (when used)
-  models = models && plans[0].t_order == 0;
+  // a target with SIP has no reach boxes: every tile visits every frame
+  const int tord = plans[0].t_order;
+  const bool boxes = models && tord == 0;
+  int msord = 0;  // the models' source order
+  for (const FramePlan &P : plans) msord = std::max(msord, P.s_order);
   const int ncx = (G.out_w + kCell - 1) / kCell, ncy = (G.out_h + kCell - 1) / kCell;
   const int64_t ncells = (int64_t)ncx * ncy;
   const int64_t nzero = 4 + 4 * (int64_t)n;  // counter padded to 16 bytes, then the boxes
   const size_t tofs = ((size_t)nzero * 4 + 255) & ~(size_t)255;
   const size_t mofs = (tofs + table + 255) & ~(size_t)255;
-  const size_t mbytes = models && !run.reach_host ? (size_t)n * ncells * sizeof(CellModel) : 0;
+  size_t mbytes = models && !run.reach_host ? (size_t)n * ncells * sizeof(CellModel) : 0;
   void *wsbuf = nullptr;
   dfr_status ws = workspace_buffer(w, mofs + mbytes, &wsbuf);
+  if (ws == DFR_E_NOMEM && tord > 0 && mbytes) {
+    // a target with SIP does without the tables: the anchored chain
+    (void)hipGetLastError();
+    models = false;
+    mbytes = 0;
+    ws = workspace_buffer(w, mofs, &wsbuf);
+  }
   if (ws != DFR_OK) return ws;
   char *dev = static_cast<char *>(wsbuf);
   int *counter = reinterpret_cast<int *>(dev);
@@ -405,7 +416,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   std::memcpy(w->host_plans, plans.data(), table);
   for (int i = 0; i < n; ++i) {
     w->host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
-    w->host_plans[i].reach = models ? reach + 4 * i : nullptr;
+    w->host_plans[i].reach = boxes ? reach + 4 * i : nullptr;
   }
   int dev_id = 0, cus = 0;
   if (hipGetDevice(&dev_id) != hipSuccess) return DFR_E_DEVICE;
@@ -416,7 +427,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   const int grid = batch_blocks_per_cu(interp, np, max_sord, lds_bytes) * cus;
   int ncx_i = ncx, ncells_i = (int)ncells, bpf = (int)((ncells + 63) / 64);
   const dim3 mgrid((unsigned)n * (unsigned)bpf);
-  const void *mkernel = cell_models_batch_ptr(max_sord);
+  const void *mkernel = cell_models_batch_ptr(msord, tord);
   void *margs[] = {&plans_dev, &ncx_i, &ncells_i, &bpf, &models_dev};
   if (!graph) {
     if (hipMemcpyAsync(plans_dev, w->host_plans, table, hipMemcpyHostToDevice, stream) !=
@@ -424,7 +435,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       return DFR_E_DEVICE;
     // counter and reach boxes start at zero; the prepass then records the boxes
     if (launch_zero_i32(counter, nzero, stream) != hipSuccess) return DFR_E_DEVICE;
-    if (models &&
+    if ((run.reach_host ? boxes : models) &&
         hipLaunchKernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
     if (run.reach_host) {
@@ -432,11 +443,11 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       // every frame may reach everywhere, reported as -1); the wait
       // also ends the frame table's copy from the pinned staging buffer,
       // which the next batch on this stream refills
-      if (models && hipMemcpyAsync(run.reach_host, reach, (size_t)16 * n, hipMemcpyDeviceToHost,
+      if (boxes && hipMemcpyAsync(run.reach_host, reach, (size_t)16 * n, hipMemcpyDeviceToHost,
                                    stream) != hipSuccess)
         return DFR_E_DEVICE;
       if (hipStreamSynchronize(stream) != hipSuccess) return DFR_E_DEVICE;
-      if (!models)
+      if (!boxes)
         for (int i = 0; i < 4 * n; ++i) run.reach_host[i] = -1;
       return DFR_OK;
     }

@@ -1,0 +1,110 @@
+"""Cell models of a target with SIP A/B (its Taylor shift about each cell,
+composed into the cell's cubic): positions against the FP64 form over every
+pixel, for every order the model instances cover and maps that mix certified
+and anchored cells; nearest must take the FP64 form's decisions.
+
+Tolerance: a certified model lies within 1e-6 px of the map, and its FP32
+coefficients and evaluation add at most gamma_7 times the magnitude of its
+terms, about 7 * 2^-24 * 50 px = 2.1e-5 px; the anchored chain is within 2e-5 px
+of it (the bound the forward parity tests use)."""
+import numpy as np
+import pytest
+import torch
+
+from synth import configs, draw_sip
+
+pytestmark = pytest.mark.gpu
+POS_TOL = 2.2e-5
+
+
+@pytest.fixture(scope="module")
+def dfr():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2505_03932_amd as d
+    return d
+
+
+def _target(tgt, order, factor, half, seed=21):
+    a, b = draw_sip(order, half, np.random.default_rng(seed))
+    return tgt.copy(a=a * factor, b=b * factor)
+
+
+# (source frame, target order, factor on the drawn distortion): orders up to 5
+# and above, small to strong; 2000 leaves cells without a certified model
+CASES = [("plain", 2, 50.0), ("plain", 3, 2000.0), ("sip", 2, 1.0), ("sip", 3, 50.0), ("sip", 5, 50.0),
+         ("sip", 6, 50.0), ("sip", 9, 50.0), ("sip7", 3, 20.0)]
+
+
+@pytest.mark.parametrize("frame,order,factor", CASES)
+@pytest.mark.parametrize("interp", ["nearest", "bilinear"])
+def test_positions_against_fp64(dfr, interp, frame, order, factor):
+    c = {"plain": lambda: configs.plain(size=300), "sip": lambda: configs.sip3(scale=0.06),
+         "sip7": lambda: configs.strong_sip()}[frame]()
+    tw = _target(c.tgt_wcs, order, factor, 0.5 * max(c.out_shape))
+    src = torch.from_numpy(c.src).cuda()
+    shape = (c.out_shape[0] - 3, c.out_shape[1] + 1)
+    print(f"target sip frame={frame} order={order} factor={factor} interp={interp}", flush=True)
+    o64, f64, p64 = dfr.reproject(src, c.src_wcs, tw, shape, interp, precision="f64",
+                                  debug_positions=True)
+    o, f, p = dfr.reproject(src, c.src_wcs, tw, shape, interp, debug_positions=True)
+    err = (p - p64).abs()
+    assert torch.equal(torch.isnan(p), torch.isnan(p64))
+    worst = err[~torch.isnan(err)].max().item()
+    print("largest position difference", worst)
+    assert worst <= POS_TOL
+    # without debug positions the unchecked interior path runs: the same bits
+    o2, f2 = dfr.reproject(src, c.src_wcs, tw, shape, interp)
+    assert torch.equal(o, o2) and torch.equal(f, f2)
+    if interp == "nearest":
+        frac = (p64 - torch.floor(p64) - 0.5).abs().amin(-1)
+        clear = ~(frac < 1e-9)
+        assert torch.equal(o[clear], o64[clear]) and torch.equal(f[clear], f64[clear])
+
+
+def test_batch_plan_and_coadd_take_the_same_models(dfr):
+    from paper_2505_03932_amd import _lib
+    from paper_2505_03932_amd.api import CWcs, _opts
+    c = configs.sip3(scale=0.06)
+    tw = _target(c.tgt_wcs, 3, 50.0, 180.0)
+    src = torch.from_numpy(c.src).cuda()
+    shape = c.out_shape
+    o, f = dfr.reproject(src, c.src_wcs, tw, shape, "bicubic")
+    outs, fps = dfr.reproject_batch([src], [c.src_wcs], tw, shape, "bicubic")
+    assert torch.equal(outs[0], o) and torch.equal(fps[0], f)
+    with dfr.Plan(src.shape, c.src_wcs, tw, shape, "bicubic") as plan:
+        po, pf = plan.execute(src)
+    assert torch.equal(po, o) and torch.equal(pf, f)
+    img, sum_wf, sum_f = dfr.coadd_batch([src], [c.src_wcs], tw, shape, "bicubic")
+    assert torch.equal(sum_f, f) and torch.equal(sum_wf, torch.where(f == 1, o, o * f))
+    # the allocation-free call keeps the chain from anchors
+    ao, af = dfr.reproject(src, c.src_wcs, tw, shape, "bicubic", precision="f32_anchor")
+    no, nf = torch.empty_like(o), torch.empty_like(f)
+    s = _lib.dfr_reproject_noalloc(src.data_ptr(), src.shape[0], src.shape[1], src.stride(0),
+                                   CWcs(c.src_wcs).s, CWcs(tw).s, shape[0], shape[1], 2,
+                                   no.data_ptr(), nf.data_ptr(), _opts(),
+                                   torch.cuda.current_stream().cuda_stream)
+    assert s == _lib.DFR_OK
+    assert torch.equal(no, ao) and torch.equal(nf, af)
+
+
+def test_captured_without_a_workspace(dfr):
+    """A target with SIP can be captured on a stream the library has not seen
+    (no table can be allocated there): the chain from anchors runs."""
+    c = configs.sip3(scale=0.06)
+    tw = _target(c.tgt_wcs, 3, 50.0, 180.0)
+    src = torch.from_numpy(c.src).cuda()
+    want, want_fp = dfr.reproject(src, c.src_wcs, tw, c.out_shape, "bilinear",
+                                  precision="f32_anchor")
+    out, fp = torch.zeros_like(want), torch.zeros_like(want)
+    dfr.release()  # no workspace is left from earlier calls
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=torch.cuda.Stream()):
+        dfr.reproject(src, c.src_wcs, tw, c.out_shape, "bilinear", out=out, fp=fp)
+    for _ in range(3):
+        out.zero_()
+        fp.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(fp, want_fp)
