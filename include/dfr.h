@@ -199,7 +199,7 @@ typedef struct dfr_frame {
 } dfr_frame;
 
 /* Reproject n frames of uneven sizes onto one target grid in a single
- * persistent launch replayed from a captured HIP graph.  outs[i] and
+ * launch of all their tiles, replayed from a HIP graph.  outs[i] and
  * footprints[i] are device [out_h][out_w] float32 (footprints or any entry
  * of it nullable).  The result of every frame is bit-identical to
  * dfr_reproject of that frame with the same options.  The graph is cached
@@ -291,7 +291,7 @@ dfr_status dfr_autotune(const float *src, int32_t src_h, int32_t src_w, int64_t 
                         int32_t out_w, dfr_interp interp, float *out, float *footprint,
                         const dfr_options *opt, void *stream, int32_t *tile);
 
-/* As dfr_autotune, for a batch (times whole persistent launches). */
+/* As dfr_autotune, for a batch (times whole launches). */
 dfr_status dfr_autotune_batch(int32_t n, const dfr_frame *frames, const dfr_wcs *tgt_wcs,
                               int32_t out_h, int32_t out_w, dfr_interp interp,
                               float *const *outs, float *const *footprints,

@@ -301,7 +301,7 @@ def _frames(srcs, wcss):
 def reproject_batch(srcs: Sequence[torch.Tensor], src_wcss, tgt_wcs, shape_out, order="bilinear",
                     *, outs=None, fps=None, footprint=True, cubic_a=-0.5, nan_outside=False,
                     tile=0, autotune=False):
-    """Reproject many frames onto one target grid in one persistent launch.
+    """Reproject many frames onto one target grid in one launch.
     Returns (outs, fps): lists of [H, W] float32 tensors."""
     srcs = [_src_tensor(s) for s in srcs]
     oh, ow = int(shape_out[0]), int(shape_out[1])

@@ -20,8 +20,9 @@ OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libdfr.so")
 ARCH = "gfx950"
 
-SOURCES = ["tiles_bilinear.hip", "tiles_bicubic.hip", "tiles_nearest.hip", "backward.hip",
-           "forward.hip", "batch.hip", "scratch.hip", "plan.cpp", "runtime.cpp", "abi.cpp"]
+SOURCES = ["stacks_bilinear.hip", "stacks_bicubic.hip", "stacks_nearest.hip", "backward.hip",
+           "tiles_bilinear.hip", "tiles_bicubic.hip", "tiles_nearest.hip", "forward.hip",
+           "batch.hip", "scratch.hip", "plan.cpp", "runtime.cpp", "abi.cpp"]
 
 CFLAGS = [
     "-O3", f"--offload-arch={ARCH}", "-std=c++17", "-fPIC", "-x", "hip",

@@ -1,10 +1,10 @@
-// Launch helpers of the persistent batch and the coadd kernels (defined in
+// Launch helpers of the batch and the coadd kernels (defined in
 // tile_kernels.hpp).
 #include "tile_kernels.hpp"
 
-namespace dfr {
+#include <algorithm>
 
-using BatchKernel = void (*)(const FramePlan *, int, TileGeom, int *);
+namespace dfr {
 
 const void *batch_kernel_ptr(int interp, int np, int sord) {
   return interp == DFR_NEAREST    ? batch_kernel_for<DFR_NEAREST>(np, sord)
@@ -24,37 +24,33 @@ const void *coadd_kernel_ptr(int interp, int np, int sord) {
                                   : coadd_kernel_for<DFR_BICUBIC>(np, sord);
 }
 
-int batch_blocks_per_cu(int interp, int np, int sord, int lds_bytes) {
-  int n = 0;
-  const void *k = batch_kernel_ptr(interp, np, sord);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, kThreads, lds_bytes) != hipSuccess ||
-      n < 1)
-    n = 1;
-  return n;
+// One work-group per item; a launch has fewer than 2^32 threads.
+static hipError_t launch_items(const void *kernel, int total, int &first, void **args, size_t lds,
+                               hipStream_t stream) {
+  for (first = 0; first < total; first += kBatchItems) {
+    const hipError_t e = hipLaunchKernel(kernel, dim3(std::min(total - first, kBatchItems)),
+                                         dim3(kThreads), args, lds, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_batch_f32(const FramePlan *plans_dev, int n_frames, int max_sord,
-                            const TileGeom &G, int interp, int np, int *counter, int grid,
-                            hipStream_t stream) {
-  hipError_t e = launch_zero_i32(counter, 1, stream);
-  if (e != hipSuccess) return e;
-  BatchKernel k = reinterpret_cast<BatchKernel>(const_cast<void *>(batch_kernel_ptr(interp, np, max_sord)));
-  size_t lds = (size_t)G.lds_cap * sizeof(float);
-  hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, stream, plans_dev, n_frames, G, counter);
-  return hipGetLastError();
+                            const TileGeom &G, int interp, int np, hipStream_t stream) {
+  int first = 0, total = n_frames * G.n_tiles;
+  TileGeom geom = G;
+  void *args[] = {&plans_dev, &first, &total, &geom};
+  return launch_items(batch_kernel_ptr(interp, np, max_sord), total, first, args,
+                      (size_t)G.lds_cap * sizeof(float), stream);
 }
 
 hipError_t launch_batch_cropped(const FramePlan *plans_dev, int n_frames, int total, int max_sord,
-                                const TileGeom &G, int interp, int np, int *counter, int grid,
-                                hipStream_t stream) {
-  hipError_t e = launch_zero_i32(counter, 1, stream);
-  if (e != hipSuccess) return e;
-  using CropKernel = void (*)(const FramePlan *, int, int, TileGeom, int *);
-  CropKernel k = reinterpret_cast<CropKernel>(const_cast<void *>(crop_kernel_ptr(interp, np, max_sord)));
-  size_t lds = (size_t)G.lds_cap * sizeof(float);
-  hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, stream, plans_dev, n_frames, total, G,
-                     counter);
-  return hipGetLastError();
+                                const TileGeom &G, int interp, int np, hipStream_t stream) {
+  int first = 0;
+  TileGeom geom = G;
+  void *args[] = {&plans_dev, &n_frames, &first, &total, &geom};
+  return launch_items(crop_kernel_ptr(interp, np, max_sord), total, first, args,
+                      (size_t)G.lds_cap * sizeof(float), stream);
 }
 
 hipError_t launch_coadd_f32(const FramePlan *plans_dev, int n_frames, int max_sord,

@@ -36,11 +36,13 @@ struct alignas(16) CellModel {
   float ex, ey;          // bound on |position - (constant + linear part)| over the cell
   int32_t bx, by;        // integer part of the source position at the cell centre
   float err;             // certified bound on |model - map| over the cell (px)
-  int32_t certified;     // 1: truncation <= kModelTol and every pixel has a valid position
+  int32_t certified;     // 1: truncation <= kModelTol and every pixel has a valid position;
+                         // kCellOut: no pixel reaches the source (the rest of the record is not set)
   float tie;             // nearest: FP32 positions this close to a rounding tie are decided in FP64
   int32_t pad_;
 };
 static_assert(sizeof(CellModel) == 112, "CellModel layout");
+constexpr int32_t kCellOut = 2;
 
 __host__ __device__ constexpr int cm_i(int k) { return k < 4 ? 0 : (k < 7 ? 1 : (k < 9 ? 2 : 3)); }
 __host__ __device__ constexpr int cm_j(int k) { return k < 4 ? k : (k < 7 ? k - 4 : (k < 9 ? k - 7 : 0)); }
@@ -371,6 +373,63 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   // (the anchored chain rounds its own coefficients alike); the tolerance
   // applies to what the cubic leaves out of the map
   M.certified = __builtin_fmax(tx, ty) <= kModelTol ? 1 : 0;
+}
+
+// Whether cell (cx, cy) of a target without SIP is certain to be found
+// without a tap in the source by both tests that follow a model (its range
+// grown by 4 px; without a certified model the anchor's test), from far fewer
+// operations than the model: |dU| <= A over the cell, and |AP| there is at
+// most SA = sum |c| (|Uc| + A)^p (|Vc| + B)^q, which bounds the constant and all
+// Taylor terms of the model together, so its range lies within A + SA + 4 of
+// the centre's affine position.  The anchor's test asks for kk < 1/2 (kap < 0.1
+// implies it), a slope below 1/4 (the same majorant differentiated) and a
+// distance of 64 |g| (1 + 2 L) + 12 at the cell's corner, where |g| is at most
+// 1.5 times the centre's: 144 |g| + 12.
+template <int SORD>
+__device__ __forceinline__ bool cell_out_of_reach(const FramePlan &P, int cx, int cy) {
+  constexpr int N = SORD >= 0 ? SORD : kMaxOrder;
+  const double h = kHalfCell;
+  const double *H = P.H;
+  const double uc = (double)cx * kCell + h - P.tcr[0], vc = (double)cy * kCell + h - P.tcr[1];
+  const double pc = fma(H[0], uc, fma(H[1], vc, H[2]));
+  const double qc = fma(H[3], uc, fma(H[4], vc, H[5]));
+  const double wc = fma(H[6], uc, fma(H[7], vc, H[8]));
+  if (!(wc > 0.0)) return false;
+  const double iw = 1.0 / wc;
+  const double Uc = pc * iw, Vc = qc * iw;
+  const float gs = (float)((fabs(H[0] - Uc * H[6]) + fabs(H[1] - Uc * H[7])) * iw);
+  const float fs = (float)((fabs(H[3] - Vc * H[6]) + fabs(H[4] - Vc * H[7])) * iw);
+  const float kap = (float)((fabs(H[6]) + fabs(H[7])) * iw * h);
+  if (!(kap < 0.1f)) return false;
+  const float A = gs * (float)h / (1.0f - kap), B = fs * (float)h / (1.0f - kap);
+  const float sinv = (float)P.s_inv_scale;
+  const float u = ((float)fabs(Uc) + A) * sinv, v = ((float)fabs(Vc) + B) * sinv;
+  float sa = 0.0f, sb = 0.0f, slope = 0.0f;  // majorants of |AP|, |BP| and of all their slopes
+  float up = 1.0f, upd = 0.0f;               // u^p, p u^(p-1)
+#pragma unroll
+  for (int p = 0; p <= N; ++p) {
+    float vq = 1.0f, vqd = 0.0f;
+#pragma unroll
+    for (int q = 0; p + q <= N; ++q) {
+      const float a = fabsf(P.fsA[tri9(p, q)]), b = fabsf(P.fsB[tri9(p, q)]);
+      const float m = up * vq;
+      sa = fmaf(a, m, sa);
+      sb = fmaf(b, m, sb);
+      slope = fmaf(a + b, fmaf(upd, vq, up * vqd), slope);
+      vqd = fmaf(vqd, v, vq);
+      vq *= v;
+    }
+    upd = fmaf(upd, u, up);
+    up *= u;
+  }
+  if (!(slope * sinv < 0.24f)) return false;
+  // FP32 rounding of the sums and positions, generously
+  const float grow = 1.0f + 1.0e-4f;
+  const float dx = (A + sa + 144.0f * gs) * grow + 24.0f + 1.0e-5f * (float)fabs(Uc);
+  const float dy = (B + sb + 144.0f * fs) * grow + 24.0f + 1.0e-5f * (float)fabs(Vc);
+  const double X = Uc + P.scr[0], Y = Vc + P.scr[1];
+  return X + dx < 0.0 || X - dx > (double)(P.src_w - 1) || Y + dy < 0.0 ||
+         Y - dy > (double)(P.src_h - 1);
 }
 
 }  // namespace dfr

@@ -40,34 +40,44 @@ __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, i
   out[i] = M;
 }
 
-// The same for every frame of a batch: block b holds 64 consecutive cells of
-// frame b / bpf (bpf blocks per frame; the frame's table starts at frame *
-// ncells).  A block belongs to one frame, so the frame's plan is read with
+// The same for every frame of a batch: block b holds 8x8 cells of frame
+// b / bpf (bpf blocks per frame, bcols of them to a row; the frame's table
+// starts at frame * ncells).  Most of a stack's grid lies outside any one
+// frame: those cells are told apart first, from a bound that costs a fraction
+// of the model, and in 8x8 blocks, so that most waves hold only cells of one
+// kind; they get no model, only the mark kCellOut.  A block belongs to one frame, so the frame's plan is read with
 // scalar loads; with cells numbered across frames the plan's address differed
 // per lane as far as the compiler knew, and every coefficient was a vector load
-// (64 frames on 8192^2, order 5: 397 us instead of 541 with the cheaper models).
+// (64 frames on 8192^2, order 5: 541 us so and with every cell modelled, 397 us
+// with scalar loads and the cheaper models, 306 us with the test).
 template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *__restrict__ plans,
-                                                              int ncx, int ncells, int bpf,
+                                                              int ncx, int ncy, int bcols,
+                                                              int bpf,
                                                               CellModel *__restrict__ out) {
-  const int frame = blockIdx.x / bpf;
-  const int c = (blockIdx.x - frame * bpf) * 64 + threadIdx.x;
-  const int cy = c / ncx, cx = c - cy * ncx;
+  const int frame = blockIdx.x / bpf, block = blockIdx.x - frame * bpf;
+  const int by = block / bcols;
+  const int cx = (block - by * bcols) * 8 + (threadIdx.x & 7), cy = by * 8 + (threadIdx.x >> 3);
+  const int64_t c = (int64_t)frame * ncx * ncy + (int64_t)cy * ncx + cx;
   // the frame table is read-only here: scalar loads through the constant
   // address space
   using ConstPlan = const __attribute__((address_space(4))) FramePlan;
   ConstPlan *cp = (ConstPlan *)(plans + frame);
   const FramePlan &P = *(const FramePlan *)cp;
   int reach = 0;
-  if (c < ncells) {
+  const bool in = cx < ncx && cy < ncy;
+  const bool reaches = P.reach != nullptr;  // reach boxes are kept (no target SIP)
+  if (in && TN == 0 && reaches && cell_out_of_reach<SORD>(P, cx, cy)) {
+    if (out) out[c].certified = kCellOut;
+  } else if (in) {
     CellModel M;
     cell_model<SORD, TN>(P, cx, cy, M);
-    if (out) out[(int64_t)frame * ncells + c] = M;  // null: only the reach boxes are wanted
+    if (out) out[c] = M;  // null: only the reach boxes are wanted
     // can any pixel of the cell have a tap inside the source?  From the
     // model's range over the whole cell, grown by 4 px (more than any tap
     // support and the tile kernel's guard); without a model, the anchor's
     // rigorous test with the widest support
-    if (P.src_w <= 0 || P.src_h <= 0 || P.reach == nullptr) {
+    if (P.src_w <= 0 || P.src_h <= 0 || !reaches) {
       reach = 0;
     } else if (!M.certified) {
       Anchor A;
@@ -82,15 +92,17 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
                yc - ry <= (float)(P.src_h - 1)) ? 1 : 0;
     }
   }
-  if (P.reach == nullptr) return;
+  if (!reaches) return;
   // the wave's reaching cells merged first
   const int v0 = wave_max(reach ? kReachBig - cx : 0), v1 = wave_max(reach ? cx + 1 : 0);
   const int v2 = wave_max(reach ? kReachBig - cy : 0), v3 = wave_max(reach ? cy + 1 : 0);
-  if (threadIdx.x == 0 && v1 > 0) {
-    atomicMax(P.reach + 0, v0);
-    atomicMax(P.reach + 1, v1);
-    atomicMax(P.reach + 2, v2);
-    atomicMax(P.reach + 3, v3);
+  // (a value that is there already needs no atomic: most blocks find theirs,
+  // and thousands of atomics on one line, which every XCD performs in memory,
+  // took longer than the models)
+  if (threadIdx.x < 4 && v1 > 0) {
+    const int v = threadIdx.x == 0 ? v0 : (threadIdx.x == 1 ? v1 : (threadIdx.x == 2 ? v2 : v3));
+    if (v > __hip_atomic_load(P.reach + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(P.reach + threadIdx.x, v);
   }
 }
 
@@ -298,8 +310,6 @@ __global__ void zero_i32_kernel(int *p, int64_t n) {
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0;
 }
-
-const void *zero_i32_kernel_ptr() { return reinterpret_cast<const void *>(zero_i32_kernel); }
 
 hipError_t launch_zero_i32(int *p, int64_t n, hipStream_t stream) {
   if (n <= 0) return hipSuccess;

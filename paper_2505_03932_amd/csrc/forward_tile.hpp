@@ -31,13 +31,12 @@ struct FwdShared {
     Anchor anchor;
     CellModel model;
   } cell[kMaxAnchors];
-  int kind[kMaxAnchors];  // 1: cell[i].model, 0: cell[i].anchor
+  int kind[kMaxAnchors];  // 1: cell[i].model, 0: cell[i].anchor, kCellOut: no pixel reaches the source
   int box[4];             // imin, imax, jmin, jmax of the source box
   int touch;              // some cell can reach the source
   int cells_ok;           // every cell has valid positions throughout
   int box_ok;             // the box is finite
   int all_model;          // every cell has a model
-  int item;               // batch: work item handed to this work-group
 };
 
 // Stage rows [bj0, bj0+bh) x columns [bi0, bi0+bw) of the source into LDS
@@ -235,7 +234,7 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
   constexpr bool TSIP = SORD == kRtOrder;
   const int tid = threadIdx.x;
   const int W = P.src_w, Hs = P.src_h;
-  int t = 0, okc = 1, kind = 0;
+  int t = 0, okc = 1, boxc = 1, kind = 0;
   int imn = 0x3fffffff, imx = -0x3fffffff, jmn = 0x3fffffff, jmx = -0x3fffffff;
   if (tid < T.nA) {
     const int cy = T.cy0 + tid / T.ncx, cx = T.cx0 + tid % T.ncx;
@@ -253,7 +252,9 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
         reinterpret_cast<u4v *>(&sh.cell[tid].model)[part] =
             global_ptr(reinterpret_cast<const u4v *>(Mg))[part];
       kind = sh.cell[tid].model.certified;
-      if (kind) {
+      if (kind == kCellOut) {
+        okc = 0;  // its pixels are uncovered: checked pixel by pixel, nothing for the box
+      } else if (kind) {
         // the model covers every pixel of the cell: the box needs only the
         // tap support (+1 px kept as a guard)
         constexpr int lo = TapSupport<INTERP>::lo + 1, hi = TapSupport<INTERP>::hi + 1;
@@ -303,6 +304,7 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
         jmx = A.by + (int)floorf(y_b) + hi;
       } else {
         okc = 0;
+        boxc = 0;
       }
     }
     sh.kind[tid] = kind;
@@ -315,11 +317,12 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
     jmx = max(jmx, __shfl_xor(jmx, m, 64));
   }
   const unsigned long long any = __ballot(t != 0), bad = __ballot(okc == 0),
+                           nobox = __ballot(boxc == 0),
                            anch = __ballot(tid < T.nA && kind == 0);
   if (tid == 0) {
     sh.touch = any != 0ull;
     sh.cells_ok = bad == 0ull;
-    sh.box_ok = bad == 0ull;
+    sh.box_ok = nobox == 0ull;
     sh.all_model = anch == 0ull;
     sh.box[0] = imn;
     sh.box[1] = imx;
@@ -434,7 +437,8 @@ __device__ __forceinline__ void tile_positions(const FramePlan &P, const TileGeo
     for (int k = 0; k < NP; ++k) {
       const int y = T.y0 + T.ty + k * T.RP;
       const int ci = ((y >> kCellLog2) - T.cy0) * T.ncx + ((xr >> kCellLog2) - T.cx0);
-      const bool mk = sh.kind[ci] != 0;
+      const int kind = sh.kind[ci];
+      const bool mk = kind != 0;
       const Anchor &A = sh.cell[ci].anchor;
       const CellModel &M = sh.cell[ci].model;
       const int bx = mk ? M.bx : A.bx, by = mk ? M.by : A.by;
@@ -452,7 +456,7 @@ __device__ __forceinline__ void tile_positions(const FramePlan &P, const TileGeo
         bool ok;
         if (mk) {
           model_at(Rw, a0 + (float)e, px, py);
-          ok = true;
+          ok = kind != kCellOut;
         } else {
           ok = pixel_position<SORD, TSIP>(P, A, tinv, sinv, (float)((xr & (kCell - 1)) + e), dy,
                                           px, py);
@@ -480,6 +484,30 @@ __device__ __forceinline__ void tile_positions(const FramePlan &P, const TileGeo
   }
 }
 
+// The interpolated value of one pixel of an interior tile: its position
+// (px, py) relative to the cell base (abx, aby) in box coordinates.
+template <int INTERP>
+__device__ __forceinline__ float interior_value(const float *__restrict__ lds, int lp, float px,
+                                                float py, int abx, int aby, float a) {
+  int i0, j0;
+  float t_, s_;
+  tap_origin<INTERP>(px, abx, i0, t_);
+  tap_origin<INTERP>(py, aby, j0, s_);
+  // i0, j0 >= 0 inside the box: one 24-bit multiply-add per pixel
+  const float *__restrict__ b = lds + __umul24(j0, lp) + i0;
+  auto fl = [&](int i, int j) -> float { return b[j * lp + i]; };
+  if constexpr (INTERP == DFR_NEAREST) {
+    return b[0];
+  } else if constexpr (INTERP == DFR_BILINEAR) {
+    return Taps<DFR_BILINEAR>::interior(0, 0, t_, s_, fl);
+  } else {
+    float wx[4], wy[4];
+    keys_weights(t_, a, wx);
+    keys_weights(s_, a, wy);
+    return Taps<DFR_BICUBIC>::interior(0, 0, wx, wy, fl);
+  }
+}
+
 // Phase 4: interpolation from the staged box (the caller has waited for its
 // DMA and synchronised), results to the sink.
 template <int INTERP, int NP, class Sink>
@@ -504,23 +532,7 @@ __device__ __forceinline__ void tile_gather(const FramePlan &P, const TileGeom &
       float o[kRun], f[kRun];
 #pragma unroll
       for (int e = 0; e < kRun; ++e) {
-        int i0, j0;
-        float t_, s_;
-        tap_origin<INTERP>(R.rx[k][e], R.abx[k], i0, t_);
-        tap_origin<INTERP>(R.ry[k][e], R.aby[k], j0, s_);
-        // i0, j0 >= 0 inside the box: one 24-bit multiply-add per pixel
-        const float *__restrict__ b = lds + __umul24(j0, lp) + i0;
-        auto fl = [&](int i, int j) -> float { return b[j * lp + i]; };
-        if constexpr (INTERP == DFR_NEAREST) {
-          o[e] = b[0];
-        } else if constexpr (INTERP == DFR_BILINEAR) {
-          o[e] = Taps<DFR_BILINEAR>::interior(0, 0, t_, s_, fl);
-        } else {
-          float wx[4], wy[4];
-          keys_weights(t_, a, wx);
-          keys_weights(s_, a, wy);
-          o[e] = Taps<DFR_BICUBIC>::interior(0, 0, wx, wy, fl);
-        }
+        o[e] = interior_value<INTERP>(lds, lp, R.rx[k][e], R.ry[k][e], R.abx[k], R.aby[k], a);
         f[e] = 1.0f;
       }
       sink.row(P, G, k, y, xr, true, o, f);

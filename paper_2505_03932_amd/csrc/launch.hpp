@@ -54,27 +54,24 @@ hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp,
 // Per-cell position models of the output grid (ncx x ncy cells of 32x32).
 hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *out,
                               hipStream_t stream);
-// Kernel (plans, ncx, ncells, bpf, out) modelling every cell of every frame
-// of a batch, bpf blocks of 64 threads per frame; sord as for the batch
+// Kernel (plans, ncx, ncy, bcols, bpf, out) modelling every cell of every
+// frame of a batch, bpf blocks of 8x8 cells per frame, bcols to a row; sord as for the batch
 // kernel, tord the target SIP order.
 const void *cell_models_batch_ptr(int sord, int tord);
 hipError_t launch_forward_f64(const FramePlan &P, const TrigPlan &T, const TileGeom &G,
                               int interp, bool trig, hipStream_t stream);
 hipError_t launch_batch_f32(const FramePlan *plans_dev, int n_frames, int max_sord,
-                            const TileGeom &G, int interp, int np, int *counter,
-                            int grid, hipStream_t stream);
+                            const TileGeom &G, int interp, int np, hipStream_t stream);
 const void *batch_kernel_ptr(int interp, int np, int sord);
 // The batch into per-frame windows (FramePlan crop, item0, tile0, ntx):
-// `total` items over the frames, persistent grid as the batch.
+// `total` items over the frames.
 hipError_t launch_batch_cropped(const FramePlan *plans_dev, int n_frames, int total, int max_sord,
-                                const TileGeom &G, int interp, int np, int *counter, int grid,
-                                hipStream_t stream);
+                                const TileGeom &G, int interp, int np, hipStream_t stream);
 // Coadd of a frame table: one work-group per target tile (G.n_tiles).
 hipError_t launch_coadd_f32(const FramePlan *plans_dev, int n_frames, int max_sord,
                             const TileGeom &G, int interp, int np, const CoaddOut &C,
                             hipStream_t stream);
-const void *zero_i32_kernel_ptr();
-int batch_blocks_per_cu(int interp, int np, int sord, int lds_bytes);
+constexpr int kBatchItems = 1 << 23;  // items of one launch of a batch kernel
 // Number of per-tile FP64 partial sums the backward kernel produces for a
 // source SIP order (9 for H, 2 for CRPIX, AP and BP monomial sums).
 inline int backward_sums(int s_order) { return 11 + (s_order + 1) * (s_order + 2); }

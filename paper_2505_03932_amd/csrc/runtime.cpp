@@ -353,8 +353,10 @@ void release_workspaces() {
     destroy_graphs(w);
     if (w.buf) (void)hipFree(w.buf);
     if (w.ctl) (void)hipFree(w.ctl);
-    if (w.host_plans) (void)hipHostFree(w.host_plans);
-    if (w.staged) (void)hipEventDestroy(w.staged);
+    for (Staging &g : w.staging) {
+      if (g.buf) (void)hipHostFree(g.buf);
+      if (g.copied) (void)hipEventDestroy(g.copied);
+    }
     it = g_ws.erase(it);
   }
 }
@@ -365,14 +367,15 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
                      int max_sord, bool models, hipStream_t stream, bool graph,
                      const BatchRun &run) {
   const CoaddOut *coadd = run.coadd;
-  if (coadd || run.crop_items >= 0 || run.reach_host) graph = false;
+  const int total = (int)plans.size() * G.n_tiles;
+  if (coadd || run.crop_items >= 0 || run.reach_host || total > kBatchItems) graph = false;
   std::lock_guard<std::mutex> lk(g_ws_mutex);
   Workspace *w = workspace(stream);
   if (!w) return DFR_E_DEVICE;
   const int n = (int)plans.size();
   const size_t table = (size_t)n * sizeof(FramePlan);
-  // counter + reach boxes (4 ints per frame, zeroed together) | frame table |
-  // per-frame model tables (when used)
+  // reach boxes (4 ints per frame, copied in as zeros with the frame table) |
+  // frame table | per-frame model tables (when used)
   // a target with SIP has no reach boxes: every tile visits every frame
   const int tord = plans[0].t_order;
   const bool boxes = models && tord == 0;
@@ -380,8 +383,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   for (const FramePlan &P : plans) msord = std::max(msord, P.s_order);
   const int ncx = (G.out_w + kCell - 1) / kCell, ncy = (G.out_h + kCell - 1) / kCell;
   const int64_t ncells = (int64_t)ncx * ncy;
-  const int64_t nzero = 4 + 4 * (int64_t)n;  // counter padded to 16 bytes, then the boxes
-  const size_t tofs = ((size_t)nzero * 4 + 255) & ~(size_t)255;
+  const size_t tofs = ((size_t)n * 16 + 255) & ~(size_t)255;
   const size_t mofs = (tofs + table + 255) & ~(size_t)255;
   size_t mbytes = models && !run.reach_host ? (size_t)n * ncells * sizeof(CellModel) : 0;
   void *wsbuf = nullptr;
@@ -395,54 +397,58 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   }
   if (ws != DFR_OK) return ws;
   char *dev = static_cast<char *>(wsbuf);
-  int *counter = reinterpret_cast<int *>(dev);
-  int32_t *reach = reinterpret_cast<int32_t *>(dev) + 4;
+  int32_t *reach = reinterpret_cast<int32_t *>(dev);
   FramePlan *plans_dev = reinterpret_cast<FramePlan *>(dev + tofs);
   CellModel *models_dev = mbytes ? reinterpret_cast<CellModel *>(dev + mofs) : nullptr;
-  // the previous batch on this stream must have copied the staged table
-  if (w->staged_pending) {
-    if (hipEventSynchronize(w->staged) != hipSuccess) return DFR_E_DEVICE;
-    w->staged_pending = false;
+  // the next staging buffer, once its last copy has ended: with one buffer a
+  // call would wait here for the whole previous batch on the stream (its copy
+  // is ordered behind that batch's kernels), so the GPU ran dry between calls
+  Staging &stage = w->staging[w->next_staging];
+  w->next_staging = (w->next_staging + 1) % kStagings;
+  if (stage.pending) {
+    if (hipEventSynchronize(stage.copied) != hipSuccess) return DFR_E_DEVICE;
+    stage.pending = false;
   }
-  if (w->host_cap < (size_t)n) {
-    if (w->host_plans) (void)hipHostFree(w->host_plans);
-    w->host_plans = nullptr;
-    w->host_cap = 0;
-    if (hipHostMalloc(reinterpret_cast<void **>(&w->host_plans), table, hipHostMallocDefault) !=
-        hipSuccess)
+  if (stage.cap < tofs + table) {
+    if (stage.buf) (void)hipHostFree(stage.buf);
+    stage.buf = nullptr;
+    stage.cap = 0;
+    if (hipHostMalloc(&stage.buf, tofs + table, hipHostMallocDefault) != hipSuccess) {
+      stage.buf = nullptr;
       return DFR_E_NOMEM;
-    w->host_cap = n;
+    }
+    stage.cap = tofs + table;
   }
-  std::memcpy(w->host_plans, plans.data(), table);
+  if (!stage.copied && hipEventCreateWithFlags(&stage.copied, hipEventDisableTiming) != hipSuccess)
+    return DFR_E_DEVICE;
+  std::memset(stage.buf, 0, tofs);
+  FramePlan *host_plans =
+      reinterpret_cast<FramePlan *>(static_cast<char *>(stage.buf) + tofs);
+  std::memcpy(host_plans, plans.data(), table);
   for (int i = 0; i < n; ++i) {
-    w->host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
-    w->host_plans[i].reach = boxes ? reach + 4 * i : nullptr;
+    host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
+    host_plans[i].reach = boxes ? reach + 4 * i : nullptr;
   }
-  int dev_id = 0, cus = 0;
-  if (hipGetDevice(&dev_id) != hipSuccess) return DFR_E_DEVICE;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id) != hipSuccess ||
-      cus < 1)
-    cus = 1;
+  // the reach boxes start at zero; the prepass then records them
+  if (hipMemcpyAsync(dev, stage.buf, tofs + table, hipMemcpyHostToDevice, stream) != hipSuccess)
+    return DFR_E_DEVICE;
+  if (hipEventRecord(stage.copied, stream) != hipSuccess) {
+    (void)hipStreamSynchronize(stream);  // the copy may still read the buffer
+    return DFR_E_DEVICE;
+  }
+  stage.pending = true;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
-  const int grid = batch_blocks_per_cu(interp, np, max_sord, lds_bytes) * cus;
-  int ncx_i = ncx, ncells_i = (int)ncells, bpf = (int)((ncells + 63) / 64);
+  int ncx_i = ncx, ncy_i = ncy, bcols = (ncx + 7) / 8, bpf = bcols * ((ncy + 7) / 8);
   const dim3 mgrid((unsigned)n * (unsigned)bpf);
   const void *mkernel = cell_models_batch_ptr(msord, tord);
-  void *margs[] = {&plans_dev, &ncx_i, &ncells_i, &bpf, &models_dev};
+  void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev};
   if (!graph) {
-    if (hipMemcpyAsync(plans_dev, w->host_plans, table, hipMemcpyHostToDevice, stream) !=
-        hipSuccess)
-      return DFR_E_DEVICE;
-    // counter and reach boxes start at zero; the prepass then records the boxes
-    if (launch_zero_i32(counter, nzero, stream) != hipSuccess) return DFR_E_DEVICE;
     if ((run.reach_host ? boxes : models) &&
         hipLaunchKernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
     if (run.reach_host) {
       // the reach boxes the prepass recorded, back to the host (none:
-      // every frame may reach everywhere, reported as -1); the wait
-      // also ends the frame table's copy from the pinned staging buffer,
-      // which the next batch on this stream refills
+      // every frame may reach everywhere, reported as -1)
       if (boxes && hipMemcpyAsync(run.reach_host, reach, (size_t)16 * n, hipMemcpyDeviceToHost,
                                    stream) != hipSuccess)
         return DFR_E_DEVICE;
@@ -455,14 +461,14 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
         coadd ? launch_coadd_f32(plans_dev, n, max_sord, G, interp, np, *coadd, stream)
         : run.crop_items >= 0
             ? launch_batch_cropped(plans_dev, n, (int)run.crop_items, max_sord, G, interp, np,
-                                   counter, grid, stream)
-            : launch_batch_f32(plans_dev, n, max_sord, G, interp, np, counter, grid, stream);
+                                   stream)
+            : launch_batch_f32(plans_dev, n, max_sord, G, interp, np, stream);
     if (e != hipSuccess) return DFR_E_DEVICE;
   } else {
     BatchGraph *found = nullptr;
     for (auto &g : w->graphs)
-      if (g.n == n && g.interp == interp && g.np == np && g.sord == max_sord && g.grid == grid &&
-          g.models == (models ? mkernel : nullptr) && g.plans_dev == plans_dev && g.plans_host == w->host_plans &&
+      if (g.n == n && g.interp == interp && g.np == np && g.sord == max_sord &&
+          g.models == (models ? mkernel : nullptr) && g.plans_dev == plans_dev &&
           std::memcmp(&g.geom, &G, sizeof(G)) == 0)
         found = &g;
     if (!found) {
@@ -473,48 +479,32 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       bg.interp = interp;
       bg.np = np;
       bg.sord = max_sord;
-      bg.grid = grid;
       bg.models = models ? mkernel : nullptr;
       bg.plans_dev = plans_dev;
-      bg.plans_host = w->host_plans;
       if (hipGraphCreate(&bg.graph, 0) != hipSuccess) return DFR_E_DEVICE;
-      hipGraphNode_t copy = nullptr, mod = nullptr, zero = nullptr, kern = nullptr;
-      bool ok = hipGraphAddMemcpyNode1D(&copy, bg.graph, nullptr, 0, plans_dev, w->host_plans,
-                                        table, hipMemcpyHostToDevice) == hipSuccess;
+      hipGraphNode_t mod = nullptr, kern = nullptr;
+      bool ok = true;
       if (models) {
         hipKernelNodeParams mp;
         std::memset(&mp, 0, sizeof(mp));
         mp.func = const_cast<void *>(mkernel);
         mp.gridDim = mgrid;
         mp.blockDim = dim3(64);
-        mp.sharedMemBytes = 0;
         mp.kernelParams = margs;
-        ok = ok && hipGraphAddKernelNode(&mod, bg.graph, &copy, 1, &mp) == hipSuccess;
+        ok = hipGraphAddKernelNode(&mod, bg.graph, nullptr, 0, &mp) == hipSuccess;
       }
-      int64_t nz = nzero;
-      void *zargs[] = {&counter, &nz};
-      hipKernelNodeParams zp;
-      std::memset(&zp, 0, sizeof(zp));
-      zp.func = const_cast<void *>(zero_i32_kernel_ptr());
-      zp.gridDim = dim3(1);
-      zp.blockDim = dim3(256);
-      zp.sharedMemBytes = 0;
-      zp.kernelParams = zargs;
-      ok = ok && hipGraphAddKernelNode(&zero, bg.graph, nullptr, 0, &zp) == hipSuccess;
       TileGeom geom = G;
-      int nf = n;
-      void *kargs[] = {&plans_dev, &nf, &geom, &counter};
+      int first = 0, nitems = total;
+      void *kargs[] = {&plans_dev, &first, &nitems, &geom};
       hipKernelNodeParams kp;
       std::memset(&kp, 0, sizeof(kp));
       kp.func = const_cast<void *>(batch_kernel_ptr(interp, np, max_sord));
-      kp.gridDim = dim3(grid);
+      kp.gridDim = dim3(total);
       kp.blockDim = dim3(kThreads);
       kp.sharedMemBytes = lds_bytes;
       kp.kernelParams = kargs;
-      hipGraphNode_t deps[2] = {models ? mod : copy, zero};
-      ok = ok && hipGraphAddKernelNode(&kern, bg.graph, deps, 2, &kp) == hipSuccess;
-      // the prepass records the reach boxes: it runs after they are zeroed
-      if (models) ok = ok && hipGraphAddDependencies(bg.graph, &zero, &mod, 1) == hipSuccess;
+      ok = ok && hipGraphAddKernelNode(&kern, bg.graph, models ? &mod : nullptr, models ? 1 : 0,
+                                       &kp) == hipSuccess;
       ok = ok && hipGraphInstantiate(&bg.exec, bg.graph, nullptr, nullptr, 0) == hipSuccess;
       if (!ok) {
         (void)hipGraphDestroy(bg.graph);
@@ -525,10 +515,6 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
     }
     if (hipGraphLaunch(found->exec, stream) != hipSuccess) return DFR_E_DEVICE;
   }
-  if (!w->staged && hipEventCreateWithFlags(&w->staged, hipEventDisableTiming) != hipSuccess)
-    return DFR_E_DEVICE;
-  if (hipEventRecord(w->staged, stream) != hipSuccess) return DFR_E_DEVICE;
-  w->staged_pending = true;
   return DFR_OK;
 }
 

@@ -49,29 +49,36 @@ void make_geom(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int
                const dfr_options &o, TileGeom &G, TileShape &ts, int lds_factor = 1);
 
 // Scratch owned by the library for one (device, stream): device memory for
-// partial sums, the batch frame table and its counter, pinned staging for
-// the frame table, and the instantiated batch graphs.  Work on one stream is
+// partial sums and the batch frame table, pinned staging for the frame table,
+// and the instantiated batch graphs.  Work on one stream is
 // ordered, so reusing the buffers call after call is safe; every function
 // here must be called with workspace_mutex() held.
 struct BatchGraph {
   TileGeom geom;
-  int n, interp, np, sord, grid;
+  int n, interp, np, sord;
   const void *models;  // the model prepass kernel, null without one
   void *plans_dev;
-  void *plans_host;
   hipGraph_t graph;
   hipGraphExec_t exec;
 };
+
+// Pinned host memory a batch's frame table is copied from; `copied` is
+// recorded after that copy.
+struct Staging {
+  void *buf = nullptr;
+  size_t cap = 0;
+  hipEvent_t copied = nullptr;
+  bool pending = false;
+};
+constexpr int kStagings = 4;  // batches that can be queued on a stream before a call waits
 
 struct Workspace {
   int device = -1;
   hipStream_t stream = nullptr;
   void *buf = nullptr;  // device scratch
   size_t cap = 0;
-  FramePlan *host_plans = nullptr;  // pinned staging of the batch frame table
-  size_t host_cap = 0;              // in frames
-  hipEvent_t staged = nullptr;      // recorded after the last batch that read host_plans
-  bool staged_pending = false;
+  Staging staging[kStagings];
+  int next_staging = 0;
   std::vector<BatchGraph> graphs;
   int *ctl = nullptr;      // backward control words: max|g| bits in two alternating slots
   int ctl_slot = 0;        // the slot the next backward call uses (zero)
@@ -99,9 +106,9 @@ struct BatchRun {
   int32_t *reach_host = nullptr;    // only the model prepass: its reach boxes, 4 per frame
 };
 
-// Reproject a batch in one persistent launch; `graph` replays a cached HIP
-// graph (frame-table copy, per-cell models of every frame when `models`,
-// counter reset, persistent kernel).  The coadd, cropped and reach-only
+// Reproject a batch in one launch of its tiles; `graph` replays a cached HIP
+// graph (per-cell models of every frame when `models`, tile kernel) after the
+// frame-table copy.  The coadd, cropped and reach-only
 // runs launch eagerly (their output pointers are kernel arguments, or the
 // host waits).
 dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int interp, int np,

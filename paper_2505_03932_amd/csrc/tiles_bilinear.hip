@@ -1,9 +1,6 @@
-// Tiled forward, batch and coadd kernels, bilinear interpolation.
+// Tiled forward kernels of the single image, bilinear interpolation.
 #include "tile_kernels.hpp"
 
 namespace dfr {
 template const void *tile_kernel_for<DFR_BILINEAR>(int, int);
-template const void *batch_kernel_for<DFR_BILINEAR>(int, int);
-template const void *coadd_kernel_for<DFR_BILINEAR>(int, int);
-template const void *crop_kernel_for<DFR_BILINEAR>(int, int);
 }  // namespace dfr
