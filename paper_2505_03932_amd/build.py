@@ -20,7 +20,8 @@ OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libdfr.so")
 ARCH = "gfx950"
 
-SOURCES = ["stacks_bilinear.hip", "stacks_bicubic.hip", "stacks_nearest.hip", "backward.hip",
+SOURCES = ["stacks_bilinear.hip", "stacks_bicubic.hip", "stacks_nearest.hip",
+           "backward_bicubic.hip", "backward_bilinear.hip", "backward_nearest.hip", "backward.hip",
            "tiles_bilinear.hip", "tiles_bicubic.hip", "tiles_nearest.hip", "forward.hip",
            "batch.hip", "scratch.hip", "plan.cpp", "runtime.cpp", "abi.cpp"]
 

@@ -91,6 +91,24 @@ struct TapSupport {
   static constexpr int hi = INTERP == DFR_NEAREST ? 0 : (INTERP == DFR_BILINEAR ? 1 : 2);
 };
 
+// Stage rows [bj0, bj0+bh) x columns [bi0, bi0+bw) of the source into LDS
+// (row stride lp) with asynchronous DMA: one wave per row, 64 columns per
+// instruction, lanes past the row end masked off.
+__device__ __forceinline__ void dma_box(const FramePlan &P, int bi0, int bj0, int bw, int bh,
+                                        int lp, float *__restrict__ lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const auto *__restrict__ s0 = global_ptr(P.src) + (int64_t)bj0 * P.pitch + bi0;
+#pragma unroll 1
+  for (int r = wave; r < bh; r += kThreads / 64) {
+    const auto *sr = s0 + (int64_t)r * P.pitch;
+#pragma unroll 1
+    for (int c0 = 0; c0 < bw; c0 += 64) {
+      if (c0 + lane < bw)
+        __builtin_amdgcn_global_load_lds(sr + c0 + lane, lds + r * lp + c0, 4, 0, 0);
+    }
+  }
+}
+
 // Output stores are streaming (non-temporal): the output is written once
 // and never read back by the kernel, so it should not evict the source
 // footprint other tiles still read from L2 and the last-level cache.

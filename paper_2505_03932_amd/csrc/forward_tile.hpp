@@ -39,24 +39,6 @@ struct FwdShared {
   int all_model;          // every cell has a model
 };
 
-// Stage rows [bj0, bj0+bh) x columns [bi0, bi0+bw) of the source into LDS
-// (row stride lp) with asynchronous DMA: one wave per row, 64 columns per
-// instruction, lanes past the row end masked off.
-__device__ __forceinline__ void dma_box(const FramePlan &P, int bi0, int bj0, int bw, int bh,
-                                        int lp, float *__restrict__ lds) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const auto *__restrict__ s0 = global_ptr(P.src) + (int64_t)bj0 * P.pitch + bi0;
-#pragma unroll 1
-  for (int r = wave; r < bh; r += kThreads / 64) {
-    const auto *sr = s0 + (int64_t)r * P.pitch;
-#pragma unroll 1
-    for (int c0 = 0; c0 < bw; c0 += 64) {
-      if (c0 + lane < bw)
-        __builtin_amdgcn_global_load_lds(sr + c0 + lane, lds + r * lp + c0, 4, 0, 0);
-    }
-  }
-}
-
 // A tile no pixel of which reaches the source: output "uncovered" (0, or
 // NaN with nan_outside) and footprint 0.
 template <int NP>
