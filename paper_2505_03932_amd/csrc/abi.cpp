@@ -592,12 +592,15 @@ dfr_status dfr_reproject_backward(const float *src, int32_t src_h, int32_t src_w
   }
   std::lock_guard<std::mutex> lk(workspace_mutex());
   Workspace *w = workspace(st);
-  // workspace: per-tile FP64 partials; for the source adjoint also the
-  // 64-bit integer sums; max|g| (as float bits) alternates between two of
-  // the workspace's control words
+  // workspace: per-tile FP64 partials; the cells' anchors; for the source
+  // adjoint also the 64-bit integer sums; max|g| (as float bits) alternates
+  // between two of the workspace's control words
   const size_t pbytes = (size_t)std::max(G.n_tiles, 1) * ns * sizeof(double);
-  const size_t qofs = (pbytes + 255) & ~(size_t)255;
-  const size_t bytes = det ? qofs + (size_t)src_h * src_w * sizeof(uint64_t) : pbytes;
+  const size_t aofs = (pbytes + 255) & ~(size_t)255;
+  const bool table = G.n_tiles > 0 && (det || G.n_tiles > kBwdAnchorTiles);
+  const size_t ncells = table ? (size_t)((out_w + kCell - 1) / kCell) * ((out_h + kCell - 1) / kCell) : 0;
+  const size_t qofs = (aofs + ncells * sizeof(Anchor) + 255) & ~(size_t)255;
+  const size_t bytes = det ? qofs + (size_t)src_h * src_w * sizeof(uint64_t) : qofs;
   void *buf = nullptr;
   int *ctl = nullptr;
   if ((s = workspace_buffer(w, bytes, &buf)) != DFR_OK) return s;
@@ -605,6 +608,7 @@ dfr_status dfr_reproject_backward(const float *src, int32_t src_h, int32_t src_w
   double *part = static_cast<double *>(buf);
   unsigned long long *qacc =
       det ? reinterpret_cast<unsigned long long *>(static_cast<char *>(buf) + qofs) : nullptr;
+  Anchor *anchors = table ? reinterpret_cast<Anchor *>(static_cast<char *>(buf) + aofs) : nullptr;
   int *gmax = ctl + w->ctl_slot, *gmax_next = ctl + (w->ctl_slot ^ 1);
   A.partials = part;
   A.n_blocks = G.n_tiles;
@@ -614,14 +618,14 @@ dfr_status dfr_reproject_backward(const float *src, int32_t src_h, int32_t src_w
   A.gsrc = grad_src;
   A.gpitch = src_w;
   A.gmax = gmax;
-  // zero the integer sums and take max|g| (one kernel), the backward, then
+  // anchors, zeroed integer sums and max|g| (one kernel), the backward, then
   // grad_src and the WCS gradient (one kernel); a launch that fails leaves
   // the control words dirty
   const bool ok =
-      (!det || launch_det_prepare(grad_out, (int64_t)out_h * out_w, qacc,
-                                  (int64_t)src_h * src_w, gmax, gmax_next, st) == hipSuccess) &&
-      (G.n_tiles <= 0 ||
-       launch_backward(P, G, (int)interp, ts.np, grad_out, part, qacc, gmax, st) == hipSuccess) &&
+      launch_bwd_prepare(P, G, (int)interp, anchors, grad_out, (int64_t)out_h * out_w, qacc,
+                         (int64_t)src_h * src_w, gmax, gmax_next, st) == hipSuccess &&
+      (G.n_tiles <= 0 || launch_backward(P, G, (int)interp, ts.np, grad_out, part, qacc, gmax,
+                                         anchors, st) == hipSuccess) &&
       launch_backward_finish(A, st) == hipSuccess;
   if (!ok) {
     w->ctl_dirty = true;

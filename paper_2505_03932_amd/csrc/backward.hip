@@ -6,7 +6,7 @@ namespace dfr {
 
 hipError_t launch_backward(const FramePlan &P, const TileGeom &G, int interp, int np,
                            const float *grad_out, double *partials, unsigned long long *src_acc,
-                           const int *gmax_bits, hipStream_t stream) {
+                           const int *gmax_bits, const Anchor *anchors, hipStream_t stream) {
   if (G.n_tiles <= 0) return hipSuccess;
   const bool tsip = P.t_order > 0;
   const bool src = src_acc != nullptr;
@@ -15,23 +15,42 @@ hipError_t launch_backward(const FramePlan &P, const TileGeom &G, int interp, in
                                          : bwd_pick<DFR_BICUBIC>(np, P.s_order, tsip, src);
   size_t lds = (size_t)G.lds_cap * sizeof(float);
   hipLaunchKernelGGL(k, dim3(G.n_tiles), dim3(kThreads), lds, stream, P, G, grad_out, partials,
-                     src_acc, gmax_bits);
+                     src_acc, gmax_bits, anchors);
   return hipGetLastError();
 }
 
-// Before the backward kernel, for the source adjoint, in one launch: the
-// 64-bit integer image is zeroed and max |g| over the output gradient is
-// folded into *gmax as the bits of a non-negative float (their integer
-// order is the float order, so atomicMax gives the same result in any
-// order).  *gmax is 0 on entry; *gmax_next, the slot the next call uses, is
-// zeroed here (the previous call's kernels, which read it, have finished).
-__global__ __launch_bounds__(256) void det_prepare_kernel(const float *__restrict__ g, int64_t n,
+// Before the backward kernel, in one launch:
+//  - the first nab blocks: the FP64 anchor of every cell, a lane each, into
+//    `anchors`.  Computed by the tiles themselves, two lanes of one wave ran
+//    that chain (about 1,500 instructions) in every group, with the other
+//    waves waiting (2048^2 bicubic: backward kernel 68.6 us that way, 64.2 so;
+//    4000x3000 bilinear 158 and 149);
+//  - the others, for the source adjoint: the 64-bit integer image is zeroed
+//    and max |g| over the output gradient is folded into *gmax as the bits of
+//    a non-negative float (their integer order is the float order, so atomicMax
+//    gives the same result in any order).  *gmax is 0 on entry; *gmax_next, the
+//    slot the next call uses, is zeroed here (the previous call's kernels,
+//    which read it, have finished).
+template <int SORD, bool TSIP>
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(FramePlan P, int ncx, int ncells,
+                                                          int support, int nab,
+                                                          Anchor *__restrict__ anchors,
+                                                          const float *__restrict__ g, int64_t n,
                                                           unsigned long long *__restrict__ q,
                                                           int64_t nq, int *__restrict__ gmax,
                                                           int *__restrict__ gmax_next) {
+  if ((int)blockIdx.x < nab) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= ncells) return;
+    const int cy = i / ncx, cx = i - cy * ncx;
+    Anchor A = Anchor{};
+    compute_anchor<SORD, TSIP>(P, cx * kCell, cy * kCell, support, A);
+    anchors[i] = A;
+    return;
+  }
   __shared__ float wm[4];
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t stride = (int64_t)(gridDim.x - nab) * 256;
+  const int64_t i0 = (int64_t)(blockIdx.x - nab) * 256 + threadIdx.x;
   if (i0 == 0) *gmax_next = 0;
   // the image is 16-byte aligned (a 256-byte aligned workspace offset)
   typedef unsigned long long u2v __attribute__((ext_vector_type(2)));
@@ -58,13 +77,32 @@ __global__ __launch_bounds__(256) void det_prepare_kernel(const float *__restric
   }
 }
 
-hipError_t launch_det_prepare(const float *grad_out, int64_t n, unsigned long long *q, int64_t nq,
+template <bool TSIP>
+static const void *prepare_pick(int sord) {
+  switch (sord) {
+    case 0: return reinterpret_cast<const void *>(bwd_prepare_kernel<0, TSIP>);
+    case 1: return reinterpret_cast<const void *>(bwd_prepare_kernel<1, TSIP>);
+    case 2: return reinterpret_cast<const void *>(bwd_prepare_kernel<2, TSIP>);
+    case 3: return reinterpret_cast<const void *>(bwd_prepare_kernel<3, TSIP>);
+    case 4: return reinterpret_cast<const void *>(bwd_prepare_kernel<4, TSIP>);
+    default: return reinterpret_cast<const void *>(bwd_prepare_kernel<5, TSIP>);
+  }
+}
+
+hipError_t launch_bwd_prepare(const FramePlan &P, const TileGeom &G, int interp, Anchor *anchors,
+                              const float *grad_out, int64_t n, unsigned long long *q, int64_t nq,
                               int *gmax, int *gmax_next, hipStream_t stream) {
+  int ncx = (G.out_w + kCell - 1) / kCell, ncells = ncx * ((G.out_h + kCell - 1) / kCell);
+  int nab = anchors ? (ncells + 255) / 256 : 0;
+  int support = interp == DFR_NEAREST ? 0 : (interp == DFR_BILINEAR ? 1 : 2);
   const int64_t work = std::max<int64_t>(n / 4, nq / 2);
-  hipLaunchKernelGGL(det_prepare_kernel,
-                     dim3((unsigned)std::min<int64_t>(512, std::max<int64_t>(1, (work + 255) / 256))),
-                     dim3(256), 0, stream, grad_out, n, q, nq, gmax, gmax_next);
-  return hipGetLastError();
+  const int blocks = q ? (int)std::min<int64_t>(512, std::max<int64_t>(1, (work + 255) / 256)) : 0;
+  if (nab + blocks == 0) return hipSuccess;
+  FramePlan plan = P;
+  void *args[] = {&plan, &ncx, &ncells, &support, &nab, &anchors,
+                  &grad_out, &n, &q, &nq, &gmax, &gmax_next};
+  const void *k = P.t_order > 0 ? prepare_pick<true>(P.s_order) : prepare_pick<false>(P.s_order);
+  return hipLaunchKernel(k, dim3(nab + blocks), dim3(256), args, 0, stream);
 }
 
 // Column c of the partials ([ns][n_blocks], column-major), summed by one

@@ -75,7 +75,8 @@ struct TileCtx {
 // (and skipping is allowed): the caller then only writes "uncovered".
 template <int INTERP, int SORD, bool TSIP, int NP>
 __device__ __forceinline__ bool tile_anchors(const FramePlan &P, const TileGeom &G, int tile,
-                                             TileShared &sh, TileCtx &c) {
+                                             const Anchor *__restrict__ anchors, TileShared &sh,
+                                             TileCtx &c) {
   const int tid = threadIdx.x;
   const int lg = G.txt_log2;
   const int TW = kRun << lg;
@@ -98,7 +99,18 @@ __device__ __forceinline__ bool tile_anchors(const FramePlan &P, const TileGeom 
     if (tid < nA) {
       const int cy = c.cy0 + tid / c.ncx, cx = c.cx0 + tid % c.ncx;
       Anchor &A = sh.anchor[tid];
-      compute_anchor<SORD, TSIP>(P, cx * kCell, cy * kCell, TapSupport<INTERP>::hi, A);
+      if (anchors && cx * kCell < G.out_w && cy * kCell < G.out_h) {
+        typedef unsigned u4v __attribute__((ext_vector_type(4)));
+        const u4v *from = reinterpret_cast<const u4v *>(
+            anchors + (int64_t)cy * ((G.out_w + kCell - 1) >> kCellLog2) + cx);
+#pragma unroll
+        for (int part = 0; part < (int)(sizeof(Anchor) / 16); ++part)
+          reinterpret_cast<u4v *>(&A)[part] = from[part];
+      } else if (anchors) {
+        A = Anchor{};  // a cell outside the output: no pixel of it is computed
+      } else {
+        compute_anchor<SORD, TSIP>(P, cx * kCell, cy * kCell, TapSupport<INTERP>::hi, A);
+      }
       t = A.touch;
       if constexpr (!TSIP) {
         // the part of the cell inside the tile and the output, as offsets from
@@ -266,6 +278,13 @@ __device__ __forceinline__ void flat_taps(int base, const float wx[4], const flo
   float gw[NT];
 #pragma unroll
   for (int k = 0; k < NT; ++k) gw[k] = gs * wx[k];
+  // every value first: between the adds, which may alias them as far as the
+  // compiler knows, each read would be waited for on its own
+  float v[NT][NT];
+#pragma unroll
+  for (int l = 0; l < NT; ++l)
+#pragma unroll
+    for (int k = 0; k < NT; ++k) v[l][k] = flat.value(base + l * flat.pitch() + k);
   float S = 0.0f, Sx = 0.0f, Sy = 0.0f;
 #pragma unroll
   for (int l = 0; l < NT; ++l) {
@@ -273,9 +292,8 @@ __device__ __forceinline__ void flat_taps(int base, const float wx[4], const flo
     float row = 0.0f, rowd = 0.0f;
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-      const float v = flat.value(rb + k);
-      row = fmaf(wx[k], v, row);
-      rowd = fmaf(dx[k], v, rowd);
+      row = fmaf(wx[k], v[l][k], row);
+      rowd = fmaf(dx[k], v[l][k], rowd);
       flat.add_scaled(rb + k, gw[k] * wy[l]);
     }
     S = fmaf(wy[l], row, S);
@@ -497,16 +515,19 @@ __device__ __forceinline__ float swap_sum(float a, float b) {
   return __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
 }
 
+// anchors: the cells' FP64 anchors from bwd_prepare_kernel, or null: each
+// group computes those of its tile.
 // SRC: the source gradient is wanted (its integer sums go to gq,
 // [src_h][src_w] dense; bwd_finish_kernel converts them); without it the
 // kernel carries no scatter code at all.
 template <int INTERP, int SORD, int NP, bool TSIP, bool SRC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NP == 1 ? 5 : 1)))
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NP == 1 || INTERP != DFR_BICUBIC ? 5 : 1)))
 void reproject_bwd(FramePlan P, TileGeom G,
                                                           const float *__restrict__ gout,
                                                           double *__restrict__ partials,
                                                           unsigned long long *__restrict__ gq,
-                                                          const int *__restrict__ gmax_bits) {
+                                                          const int *__restrict__ gmax_bits,
+                                                          const Anchor *__restrict__ anchors) {
   constexpr int NC = (SORD + 1) * (SORD + 2) / 2;
   constexpr int NS = 11 + 2 * NC;
   extern __shared__ __align__(16) float lds[];
@@ -530,7 +551,7 @@ void reproject_bwd(FramePlan P, TileGeom G,
       load_run(gout + (int64_t)y * G.out_w + xr, y < G.out_h ? G.out_w - xr : 0, gr[k]);
     }
   }
-  if (tile_anchors<INTERP, SORD, TSIP, NP>(P, G, tile, sh, c)) {
+  if (tile_anchors<INTERP, SORD, TSIP, NP>(P, G, tile, anchors, sh, c)) {
     TilePos<NP> T;
     const int W = P.src_w, Hs = P.src_h;
     constexpr bool want_src = SRC;
@@ -732,7 +753,7 @@ void reproject_bwd(FramePlan P, TileGeom G,
 }
 
 using BwdKernel = void (*)(FramePlan, TileGeom, const float *, double *, unsigned long long *,
-                          const int *);
+                          const int *, const Anchor *);
 
 template <int INTERP, int NP, bool TSIP, bool SRC>
 BwdKernel bwd_sord(int sord) {

@@ -81,15 +81,20 @@ struct WcsJacobian {
 };
 
 // src_acc non-null: the source adjoint too, as integer sums into src_acc
-// [src_h][src_w] (zeroed by launch_det_prepare), quantised with the scale
+// [src_h][src_w] (zeroed by launch_bwd_prepare), quantised with the scale
 // from max|g| in gmax_bits; launch_backward_finish then writes grad_src.
 hipError_t launch_backward(const FramePlan &P, const TileGeom &G, int interp, int np,
                            const float *grad_out, double *partials, unsigned long long *src_acc,
-                           const int *gmax_bits, hipStream_t stream);
-// Zero q[0 .. nq) and *gmax_next, and fold max |g| into *gmax (which must
-// start at 0).
-hipError_t launch_det_prepare(const float *grad_out, int64_t n, unsigned long long *q, int64_t nq,
+                           const int *gmax_bits, const Anchor *anchors, hipStream_t stream);
+// What precedes it: the cells' anchors (anchors non-null), and for the source
+// adjoint (q non-null) q[0 .. nq) and *gmax_next zeroed and max |g| folded into
+// *gmax (which must start at 0).
+hipError_t launch_bwd_prepare(const FramePlan &P, const TileGeom &G, int interp, Anchor *anchors,
+                              const float *grad_out, int64_t n, unsigned long long *q, int64_t nq,
                               int *gmax, int *gmax_next, hipStream_t stream);
+// A backward call without the source adjoint needs that launch only for the
+// anchors: above this many tiles it pays (one round of groups on the chip).
+constexpr int kBwdAnchorTiles = 1024;
 // What follows the backward kernel: the WCS partials reduced and chained
 // into grad_wcs (nr = ns - 10 blocks when grad_wcs is wanted, else 0), and
 // the integer sums q (if non-null) converted into grad_src with the scale
