@@ -116,11 +116,11 @@ void coadd_tiles(const FramePlan *__restrict__ plans, int n_frames, TileGeom G, 
   extern __shared__ float lds[];
   __shared__ FwdShared sh;
   // Work per tile follows the stack's depth there, which varies across the
-  // target (deep in the middle, zero at the edges): consecutive blocks, which
-  // the dispatcher deals round-robin to the XCDs, take consecutive tiles, so
-  // every XCD gets a share of each region (contiguous per-XCD bands would
-  // leave the XCDs holding the edges idle).
-  const int tile = blockIdx.x;
+  // target (deep in the middle, zero at the edges): short runs of tiles, which
+  // share source rows, go round the XCDs (contiguous per-XCD bands would leave
+  // the XCDs holding the edges idle).  With the shorter DMA loop 64 frames on
+  // 8192^2 take this kernel 2,400 us, from 2,690 with tile b for block b.
+  const int tile = batch_item(blockIdx.x, 16, G.n_tiles);
   const int lg = G.txt_log2;
   const int TW = kRun << lg, RP = kThreads >> lg, TH = RP * NP;
   const int trow = tile / G.tiles_x;
