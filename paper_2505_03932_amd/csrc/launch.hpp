@@ -13,10 +13,31 @@ constexpr int kTileCount = 12;
 constexpr int kDefaultTile = 5;  // 64 x 32
 constexpr int kCoaddTile = 5;    // coadd default
 
-// Untuned default tile of the forward kernels (single image, plan, batch),
-// measured on the 6000x4000 SIP-3 frame: 128 x 16 for nearest and bilinear,
-// 32 x 64 for bicubic.
-inline int forward_default_tile(int interp) { return interp == DFR_BICUBIC ? 2 : 8; }
+// Untuned default tile of the forward kernels for n images of out_h x out_w
+// (1 for a single image or a plan).  Tile kernel alone, us, by tile shape:
+//                         32x32  64x16  64x32  32x64  128x16
+//   256^2      bilinear     6.4    6.3    8.9    9.1    9.1
+//   256^2      bicubic      8.5    8.2   13.5   13.2   13.9
+//   2048^2     nearest     18.2   18.5   15.9   15.1   16.2
+//   2048^2     bilinear    14.5   14.8   17.4   14.8   17.6
+//   2048^2     bicubic     19.0   20.2   21.0   20.0   25.8
+//   2900x2400  bilinear    25.8   21.3   25.6   33.4   22.9
+//   2900x2400  bicubic     29.5   28.6   30.0   37.0   35.1
+//   5003x3301  bicubic     76.1   69.5   65.8   96.6   70.0
+//   6000x4000  bilinear    76.8   73.2   67.1   71.7   64.6
+//   6000x4000  bicubic     94.7   98.8   79.3   76.3   96.1
+// Up to a few rounds of groups on the chip (256 CUs x 8 groups x 1024 pixels a
+// round) a call is as long as one group's chain of phases: the smallest tiles,
+// one row per thread, win (nearest, with the least to do per pixel, only below
+// one round).  Beyond, bytes count: tiles with fewer halo rows, and wide ones
+// where output rows are not multiples of 128 bytes (a narrow tile then splits
+// a line at both ends of every row).
+inline int forward_default_tile(int interp, int64_t n, int64_t out_h, int64_t out_w) {
+  const int64_t px = n * out_h * out_w;
+  const bool lines = (out_w & 31) == 0;
+  if (px <= (interp == DFR_NEAREST ? int64_t(1) << 20 : int64_t(1) << 23)) return lines ? 1 : 4;
+  return interp == DFR_BICUBIC ? (lines ? 2 : kDefaultTile) : 8;
+}
 // The backward's, measured on the 2048^2 bicubic and 6000x4000 bilinear
 // cases: 64 x 16 (one row per thread) for bicubic with the source gradient
 // (its LDS adds), else 64 x 32.

@@ -115,7 +115,7 @@ void tune_store(const std::string &key, int tile) {
 }
 
 int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int requested,
-                bool batch, int lds_factor, int pref) {
+                bool batch, int lds_factor, int pref, int64_t images) {
   if (requested >= 1 && requested <= kTileCount) return requested;
   {
     std::lock_guard<std::mutex> lk(g_tune_mutex);
@@ -132,7 +132,7 @@ int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, in
   // per output pixel still: 218 against 225 us on the 8192^2 frame rotated
   // by 45 degrees), else the largest tile whose box does
   {
-    if (pref < 1 || pref > kTileCount) pref = forward_default_tile(interp);
+    if (pref < 1 || pref > kTileCount) pref = forward_default_tile(interp, images, out_h, out_w);
     TileShape a, b;
     tile_shape(pref, a);
     tile_shape(kDefaultTile, b);
