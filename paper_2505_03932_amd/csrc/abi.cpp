@@ -240,9 +240,13 @@ dfr_status dfr_reproject(const float *src, int32_t src_h, int32_t src_w, int64_t
     TileShape ts;
     single_setup(src, src_h, src_w, src_pitch, *src_wcs, *tgt_wcs, out_h, out_w, out, footprint,
                  (int)interp, o, P, G, ts);
-    std::lock_guard<std::mutex> lk(workspace_mutex());
-    if ((s = models_for(P, out_h, out_w, o, st)) != DFR_OK) return s;
-    e = launch_forward_f32(P, G, (int)interp, ts.np, st);
+    if (o.precision == DFR_PREC_F32 && forward_small(P, G, ts.np)) {
+      e = launch_forward_small(P, G, (int)interp, st);
+    } else {
+      std::lock_guard<std::mutex> lk(workspace_mutex());
+      if ((s = models_for(P, out_h, out_w, o, st)) != DFR_OK) return s;
+      e = launch_forward_f32(P, G, (int)interp, ts.np, st);
+    }
   } else {
     build_plan(src, src_h, src_w, src_pitch, *src_wcs, *tgt_wcs, out_h, out_w, out, footprint, P);
     TrigPlan T;
@@ -277,6 +281,8 @@ dfr_status dfr_reproject_noalloc(const float *src, int32_t src_h, int32_t src_w,
     single_setup(src, src_h, src_w, src_pitch, *src_wcs, *tgt_wcs, out_h, out_w, out, footprint,
                  (int)interp, o, P, G, ts);
     P.models = nullptr;
+    if (o.precision == DFR_PREC_F32 && forward_small(P, G, ts.np))
+      return launch_forward_small(P, G, (int)interp, st) == hipSuccess ? DFR_OK : DFR_E_DEVICE;
     // (a target with SIP takes the anchored chain here: its calls need no
     // scratch, so they have no limit and may overlap)
     if (o.precision == DFR_PREC_F32 && P.t_order == 0) {

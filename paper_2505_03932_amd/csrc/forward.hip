@@ -15,6 +15,23 @@ static TileKernel pick_tile_kernel(int interp, int np, int sord) {
   return reinterpret_cast<TileKernel>(const_cast<void *>(k));
 }
 
+bool forward_small(const FramePlan &P, const TileGeom &G, int np) {
+  return np == 1 && G.n_tiles <= kSmallTiles && P.t_order == 0 && P.s_order <= 5;
+}
+
+hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int interp,
+                                hipStream_t stream) {
+  if (G.n_tiles <= 0) return hipSuccess;
+  const void *k = interp == DFR_NEAREST    ? small_kernel_for<DFR_NEAREST>(P.s_order)
+                  : interp == DFR_BILINEAR ? small_kernel_for<DFR_BILINEAR>(P.s_order)
+                                           : small_kernel_for<DFR_BICUBIC>(P.s_order);
+  FramePlan plan = P;
+  TileGeom geom = G;
+  void *args[] = {&plan, &geom};
+  return hipLaunchKernel(k, dim3(G.n_tiles), dim3(kThreads), args,
+                         (size_t)G.lds_cap * sizeof(float), stream);
+}
+
 hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp, int np,
                               hipStream_t stream) {
   if (G.n_tiles <= 0) return hipSuccess;

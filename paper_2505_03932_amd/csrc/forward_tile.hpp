@@ -210,7 +210,8 @@ __device__ __forceinline__ int64_t tile_cell_index(const TileGeom &G, const Tile
 // the tile's flags, into sh.
 // The target SIP is compiled only into the run-time-order variant (the
 // launcher uses it whenever the target WCS has A/B).
-template <int INTERP, int SORD, int NP>
+// OWN: the models are made here instead of read from a table.
+template <int INTERP, int SORD, int NP, bool OWN>
 __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G, const TileXY &T,
                                            FwdShared &sh) {
   constexpr bool TSIP = SORD == kRtOrder;
@@ -226,13 +227,19 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
       // pixels is computed, it has no model-table entry and adds nothing to
       // the box (its sh.cell slot is never read for a valid pixel)
       kind = 1;
-    } else if (P.models) {
-      const CellModel *Mg = P.models + tile_cell_index(G, T, tid);
-      typedef unsigned u4v __attribute__((ext_vector_type(4)));
+    } else if (OWN || P.models) {
+      if constexpr (OWN) {
+        CellModel M;
+        cell_model<SORD>(P, cx, cy, M);
+        sh.cell[tid].model = M;
+      } else {
+        const CellModel *Mg = P.models + tile_cell_index(G, T, tid);
+        typedef unsigned u4v __attribute__((ext_vector_type(4)));
 #pragma unroll
-      for (int part = 0; part < (int)(sizeof(CellModel) / 16); ++part)
-        reinterpret_cast<u4v *>(&sh.cell[tid].model)[part] =
-            global_ptr(reinterpret_cast<const u4v *>(Mg))[part];
+        for (int part = 0; part < (int)(sizeof(CellModel) / 16); ++part)
+          reinterpret_cast<u4v *>(&sh.cell[tid].model)[part] =
+              global_ptr(reinterpret_cast<const u4v *>(Mg))[part];
+      }
       kind = sh.cell[tid].model.certified;
       if (kind == kCellOut) {
         okc = 0;  // its pixels are uncovered: checked pixel by pixel, nothing for the box
@@ -638,12 +645,12 @@ __device__ __forceinline__ void nearest_ties(const FramePlan &P, const TileGeom 
 }
 
 // One tile of one frame: the four phases in order.
-template <int INTERP, int SORD, int NP, class Sink>
+template <int INTERP, int SORD, int NP, bool OWN = false, class Sink>
 __device__ __forceinline__ void forward_tile(const FramePlan &P, const TileGeom &G, int tile,
                                              float *__restrict__ lds, FwdShared &sh, Sink &sink) {
   constexpr bool kDefer = INTERP == DFR_NEAREST && Sink::kDeferTies;
   const TileXY T = tile_xy<NP>(G, tile);
-  if ((threadIdx.x >> 6) == 0) tile_cells<INTERP, SORD, NP>(P, G, T, sh);
+  if ((threadIdx.x >> 6) == 0) tile_cells<INTERP, SORD, NP, OWN>(P, G, T, sh);
   __syncthreads();
   if (!sh.touch && G.allow_skip) {
     sink.template uncovered<NP>(P, G, tile);

@@ -72,6 +72,13 @@ struct TrigPlan {
 
 hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp, int np,
                               hipStream_t stream);
+// Whether a call with cell models takes the one-launch form for few tiles
+// (launch_forward_small, no model table): tiles of one row per thread, up to
+// the groups that run at once beside the FP64 registers.
+constexpr int kSmallTiles = 768;
+bool forward_small(const FramePlan &P, const TileGeom &G, int np);
+hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int interp,
+                                hipStream_t stream);
 // Per-cell position models of the output grid (ncx x ncy cells of 32x32).
 hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *out,
                               hipStream_t stream);

@@ -24,6 +24,19 @@ void reproject_tiles(FramePlan P, TileGeom G) {
   forward_tile<INTERP, SORD, NP>(P, G, xcd_tile(blockIdx.x, G.n_tiles), lds, sh, sink);
 }
 
+// The same with each group making the models of its own cells (32x32 and
+// 64x16 tiles: one or two of them), for outputs of few tiles: one launch and no
+// table.  The FP64 chain is then on every group's path, but while the groups
+// are few they all run at once, so it costs its own latency (about 2 us) in
+// place of a launch that waits for another one (@FUSE@).
+template <int INTERP, int SORD>
+__global__ __launch_bounds__(kThreads) void reproject_small(FramePlan P, TileGeom G) {
+  extern __shared__ float lds[];
+  __shared__ FwdShared sh;
+  StoreSink sink;
+  forward_tile<INTERP, SORD, 1, true>(P, G, xcd_tile(blockIdx.x, G.n_tiles), lds, sh, sink);
+}
+
 // Order in which the work-groups of a batch take its items ((frame, tile)
 // pairs): groups are dealt round-robin to the 8 XCDs, each with its own L2, so
 // each XCD gets runs of `chunk` consecutive items (a few rows of tiles, which
@@ -183,6 +196,10 @@ struct TileK {
   static const void *ptr() { return reinterpret_cast<const void *>(reproject_tiles<INTERP, SORD, NP>); }
 };
 template <int INTERP, int SORD, int NP>
+struct SmallK {
+  static const void *ptr() { return reinterpret_cast<const void *>(reproject_small<INTERP, SORD>); }
+};
+template <int INTERP, int SORD, int NP>
 struct BatchK {
   static const void *ptr() { return reinterpret_cast<const void *>(reproject_batch<INTERP, SORD, NP>); }
 };
@@ -203,6 +220,19 @@ const void *tile_kernel_for(int np, int sord) {
     case 1: return pick_sord<TileK, INTERP, 1>(sord);
     case 2: return pick_sord<TileK, INTERP, 2>(sord);
     default: return pick_sord<TileK, INTERP, 4>(sord);
+  }
+}
+
+// reproject_small for source orders 0 .. 5.
+template <int INTERP>
+const void *small_kernel_for(int sord) {
+  switch (sord) {
+    case 0: return SmallK<INTERP, 0, 1>::ptr();
+    case 1: return SmallK<INTERP, 1, 1>::ptr();
+    case 2: return SmallK<INTERP, 2, 1>::ptr();
+    case 3: return SmallK<INTERP, 3, 1>::ptr();
+    case 4: return SmallK<INTERP, 4, 1>::ptr();
+    default: return SmallK<INTERP, 5, 1>::ptr();
   }
 }
 
@@ -236,6 +266,9 @@ const void *coadd_kernel_for(int np, int sord) {
 extern template const void *tile_kernel_for<DFR_NEAREST>(int, int);
 extern template const void *tile_kernel_for<DFR_BILINEAR>(int, int);
 extern template const void *tile_kernel_for<DFR_BICUBIC>(int, int);
+extern template const void *small_kernel_for<DFR_NEAREST>(int);
+extern template const void *small_kernel_for<DFR_BILINEAR>(int);
+extern template const void *small_kernel_for<DFR_BICUBIC>(int);
 extern template const void *batch_kernel_for<DFR_NEAREST>(int, int);
 extern template const void *batch_kernel_for<DFR_BILINEAR>(int, int);
 extern template const void *batch_kernel_for<DFR_BICUBIC>(int, int);

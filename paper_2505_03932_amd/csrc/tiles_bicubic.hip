@@ -3,4 +3,5 @@
 
 namespace dfr {
 template const void *tile_kernel_for<DFR_BICUBIC>(int, int);
+template const void *small_kernel_for<DFR_BICUBIC>(int);
 }  // namespace dfr

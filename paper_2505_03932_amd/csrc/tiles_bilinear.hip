@@ -3,4 +3,5 @@
 
 namespace dfr {
 template const void *tile_kernel_for<DFR_BILINEAR>(int, int);
+template const void *small_kernel_for<DFR_BILINEAR>(int);
 }  // namespace dfr

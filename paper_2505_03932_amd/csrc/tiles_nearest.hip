@@ -3,4 +3,5 @@
 
 namespace dfr {
 template const void *tile_kernel_for<DFR_NEAREST>(int, int);
+template const void *small_kernel_for<DFR_NEAREST>(int);
 }  // namespace dfr
