@@ -298,8 +298,8 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
     }
     sh.kind[tid] = kind;
   }
-#pragma unroll
-  for (int m = kMaxAnchors / 2; m >= 1; m >>= 1) {
+#pragma unroll 1
+  for (int m = 1; m < T.nA; m <<= 1) {  // (a power of two cells: lane 0 ends with all)
     imn = min(imn, __shfl_xor(imn, m, 64));
     imx = max(imx, __shfl_xor(imx, m, 64));
     jmn = min(jmn, __shfl_xor(jmn, m, 64));
@@ -474,16 +474,17 @@ __device__ __forceinline__ void tile_positions(const FramePlan &P, const TileGeo
 }
 
 // The interpolated value of one pixel of an interior tile: its position
-// (px, py) relative to the cell base (abx, aby) in box coordinates.
+// (px, py) relative to its cell's base, whose byte offset in the staged box is
+// `base` (once per run: a pixel then adds one shift-add and one multiply-add).
 template <int INTERP>
 __device__ __forceinline__ float interior_value(const float *__restrict__ lds, int lp, float px,
-                                                float py, int abx, int aby, float a) {
+                                                float py, int base, float a) {
   int i0, j0;
   float t_, s_;
-  tap_origin<INTERP>(px, abx, i0, t_);
-  tap_origin<INTERP>(py, aby, j0, s_);
-  // i0, j0 >= 0 inside the box: one 24-bit multiply-add per pixel
-  const float *__restrict__ b = lds + __umul24(j0, lp) + i0;
+  tap_origin<INTERP>(px, 0, i0, t_);
+  tap_origin<INTERP>(py, 0, j0, s_);
+  const float *__restrict__ b = reinterpret_cast<const float *>(
+      reinterpret_cast<const char *>(lds) + (__mul24(j0, 4 * lp) + (4 * i0 + base)));
   auto fl = [&](int i, int j) -> float { return b[j * lp + i]; };
   if constexpr (INTERP == DFR_NEAREST) {
     return b[0];
@@ -518,10 +519,11 @@ __device__ __forceinline__ void tile_gather(const FramePlan &P, const TileGeom &
 #pragma unroll
     for (int k = 0; k < NP; ++k) {
       const int y = T.y0 + T.ty + k * T.RP;
+      const int base = 4 * (R.aby[k] * lp + R.abx[k]);
       float o[kRun], f[kRun];
 #pragma unroll
       for (int e = 0; e < kRun; ++e) {
-        o[e] = interior_value<INTERP>(lds, lp, R.rx[k][e], R.ry[k][e], R.abx[k], R.aby[k], a);
+        o[e] = interior_value<INTERP>(lds, lp, R.rx[k][e], R.ry[k][e], base, a);
         f[e] = 1.0f;
       }
       sink.row(P, G, k, y, xr, true, o, f);

@@ -28,7 +28,8 @@ void reproject_tiles(FramePlan P, TileGeom G) {
 // 64x16 tiles: one or two of them), for outputs of few tiles: one launch and no
 // table.  The FP64 chain is then on every group's path, but while the groups
 // are few they all run at once, so it costs its own latency (about 2 us) in
-// place of a launch that waits for another one (@FUSE@).
+// place of a launch that waits for another one (256x256 bilinear: 15.2 us per
+// call with the table, 12.4 so; 487x500 alignment step 43.6 and 40.1).
 template <int INTERP, int SORD>
 __global__ __launch_bounds__(kThreads) void reproject_small(FramePlan P, TileGeom G) {
   extern __shared__ float lds[];
