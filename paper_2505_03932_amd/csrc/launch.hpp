@@ -12,6 +12,8 @@ namespace dfr {
 constexpr int kTileCount = 12;
 constexpr int kDefaultTile = 5;  // 64 x 32
 constexpr int kCoaddTile = 5;    // coadd default
+constexpr int kSquareTile = 6;   // 64 x 64, four rows per thread
+constexpr int kFlatTile = 8;     // 128 x 16
 
 // Untuned default tile of the forward kernels for n images of out_h x out_w
 // (1 for a single image or a plan).  Tile kernel alone, us, by tile shape:
@@ -36,7 +38,7 @@ inline int forward_default_tile(int interp, int64_t n, int64_t out_h, int64_t ou
   const int64_t px = n * out_h * out_w;
   const bool lines = (out_w & 31) == 0;
   if (px <= (interp == DFR_NEAREST ? int64_t(1) << 20 : int64_t(1) << 23)) return lines ? 1 : 4;
-  return interp == DFR_BICUBIC ? (lines ? 2 : kDefaultTile) : 8;
+  return interp == DFR_BICUBIC ? (lines ? 2 : kDefaultTile) : kFlatTile;
 }
 // The backward's, measured on the 2048^2 bicubic and 6000x4000 bilinear
 // cases: 64 x 16 (one row per thread) for bicubic with the source gradient
