@@ -62,16 +62,18 @@ __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, i
 // starts at frame * ncells).  Most of a stack's grid lies outside any one
 // frame: those cells are told apart first, from a bound that costs a fraction
 // of the model, and in 8x8 blocks, so that most waves hold only cells of one
-// kind; they get no model, only the mark kCellOut.  A block belongs to one frame, so the frame's plan is read with
-// scalar loads; with cells numbered across frames the plan's address differed
+// kind; they get no model, only the mark kCellOut.  A block belongs to one
+// frame, so the frame's plan is read with scalar loads; with cells numbered across frames the plan's address differed
 // per lane as far as the compiler knew, and every coefficient was a vector load
 // (64 frames on 8192^2, order 5: 541 us so and with every cell modelled, 397 us
-// with scalar loads and the cheaper models, 306 us with the test).
+// with scalar loads and the cheaper models, 306 us with the test, 200 us since
+// reach_kernel folds the boxes).
 template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *__restrict__ plans,
                                                               int ncx, int ncy, int bcols,
                                                               int bpf,
-                                                              CellModel *__restrict__ out) {
+                                                              CellModel *__restrict__ out,
+                                                              int4 *__restrict__ parts) {
   const int frame = blockIdx.x / bpf, block = blockIdx.x - frame * bpf;
   const int by = block / bcols;
   const int cx = (block - by * bcols) * 8 + (threadIdx.x & 7), cy = by * 8 + (threadIdx.x >> 3);
@@ -110,18 +112,39 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
     }
   }
   if (!reaches) return;
-  // the wave's reaching cells merged first
+  // the block's box, for reach_kernel
   const int v0 = wave_max(reach ? kReachBig - cx : 0), v1 = wave_max(reach ? cx + 1 : 0);
   const int v2 = wave_max(reach ? kReachBig - cy : 0), v3 = wave_max(reach ? cy + 1 : 0);
-  // (a value that is there already needs no atomic: most blocks find theirs,
-  // and thousands of atomics on one line, which every XCD performs in memory,
-  // took longer than the models)
-  if (threadIdx.x < 4 && v1 > 0) {
-    const int v = threadIdx.x == 0 ? v0 : (threadIdx.x == 1 ? v1 : (threadIdx.x == 2 ? v2 : v3));
-    if (v > __hip_atomic_load(P.reach + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(P.reach + threadIdx.x, v);
+  if (threadIdx.x == 0) parts[blockIdx.x] = make_int4(v0, v1, v2, v3);
+}
+
+// A frame's reach box from those of its blocks, one group per frame.  (Blocks
+// folding theirs into the frame's with atomics, or only with a look at it
+// before, met on one line that every XCD reads and writes in memory: the
+// models of 64 frames on 8192^2 took 297 us so, 195 and 5 us without.)
+__global__ __launch_bounds__(256) void reach_kernel(const FramePlan *__restrict__ plans,
+                                                    const int4 *__restrict__ parts, int bpf) {
+  __shared__ int4 wm[4];
+  int4 m = make_int4(0, 0, 0, 0);
+  for (int i = threadIdx.x; i < bpf; i += 256) {
+    const int4 v = parts[(int64_t)blockIdx.x * bpf + i];
+    m.x = max(m.x, v.x);
+    m.y = max(m.y, v.y);
+    m.z = max(m.z, v.z);
+    m.w = max(m.w, v.w);
+  }
+  m = make_int4(wave_max(m.x), wave_max(m.y), wave_max(m.z), wave_max(m.w));
+  if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t *r = plans[blockIdx.x].reach;
+    r[0] = max(max(wm[0].x, wm[1].x), max(wm[2].x, wm[3].x));
+    r[1] = max(max(wm[0].y, wm[1].y), max(wm[2].y, wm[3].y));
+    r[2] = max(max(wm[0].z, wm[1].z), max(wm[2].z, wm[3].z));
+    r[3] = max(max(wm[0].w, wm[1].w), max(wm[2].w, wm[3].w));
   }
 }
+const void *reach_kernel_ptr() { return reinterpret_cast<const void *>(reach_kernel); }
 
 // Instances: source orders 0 .. 5 (and any) for a target without SIP; with
 // target SIP both orders up to 5, or any (padding with zero coefficients is

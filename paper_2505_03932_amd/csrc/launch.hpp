@@ -84,10 +84,12 @@ hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int inter
 // Per-cell position models of the output grid (ncx x ncy cells of 32x32).
 hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *out,
                               hipStream_t stream);
-// Kernel (plans, ncx, ncy, bcols, bpf, out) modelling every cell of every
-// frame of a batch, bpf blocks of 8x8 cells per frame, bcols to a row; sord as for the batch
+// Kernel (plans, ncx, ncy, bcols, bpf, out, parts) modelling every cell of
+// every frame of a batch, bpf blocks of 8x8 cells per frame, bcols to a row; sord as for the batch
 // kernel, tord the target SIP order.
 const void *cell_models_batch_ptr(int sord, int tord);
+// Kernel (plans, parts, bpf) folding its blocks' reach boxes, a group per frame.
+const void *reach_kernel_ptr();
 hipError_t launch_forward_f64(const FramePlan &P, const TrigPlan &T, const TileGeom &G,
                               int interp, bool trig, hipStream_t stream);
 hipError_t launch_batch_f32(const FramePlan *plans_dev, int n_frames, int max_sord,

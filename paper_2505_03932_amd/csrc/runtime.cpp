@@ -386,8 +386,8 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   if (!w) return DFR_E_DEVICE;
   const int n = (int)plans.size();
   const size_t table = (size_t)n * sizeof(FramePlan);
-  // reach boxes (4 ints per frame, copied in as zeros with the frame table) |
-  // frame table | per-frame model tables (when used)
+  // reach boxes (4 ints per frame) | frame table | reach boxes of the models'
+  // blocks | per-frame model tables (when used)
   // a target with SIP has no reach boxes: every tile visits every frame
   const int tord = plans[0].t_order;
   const bool boxes = models && tord == 0;
@@ -396,7 +396,9 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   const int ncx = (G.out_w + kCell - 1) / kCell, ncy = (G.out_h + kCell - 1) / kCell;
   const int64_t ncells = (int64_t)ncx * ncy;
   const size_t tofs = ((size_t)n * 16 + 255) & ~(size_t)255;
-  const size_t mofs = (tofs + table + 255) & ~(size_t)255;
+  int ncx_i = ncx, ncy_i = ncy, bcols = (ncx + 7) / 8, bpf = bcols * ((ncy + 7) / 8);
+  const size_t pofs = (tofs + table + 255) & ~(size_t)255;
+  const size_t mofs = (pofs + (boxes ? (size_t)n * bpf * sizeof(int4) : 0) + 255) & ~(size_t)255;
   size_t mbytes = models && !run.reach_host ? (size_t)n * ncells * sizeof(CellModel) : 0;
   void *wsbuf = nullptr;
   dfr_status ws = workspace_buffer(w, mofs + mbytes, &wsbuf);
@@ -441,7 +443,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
     host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
     host_plans[i].reach = boxes ? reach + 4 * i : nullptr;
   }
-  // the reach boxes start at zero; the prepass then records them
+  // (the reach boxes' place goes with it, zero; the prepass writes them)
   if (hipMemcpyAsync(dev, stage.buf, tofs + table, hipMemcpyHostToDevice, stream) != hipSuccess)
     return DFR_E_DEVICE;
   if (hipEventRecord(stage.copied, stream) != hipSuccess) {
@@ -450,13 +452,18 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   }
   stage.pending = true;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
-  int ncx_i = ncx, ncy_i = ncy, bcols = (ncx + 7) / 8, bpf = bcols * ((ncy + 7) / 8);
+  int4 *parts = reinterpret_cast<int4 *>(dev + pofs);
   const dim3 mgrid((unsigned)n * (unsigned)bpf);
   const void *mkernel = cell_models_batch_ptr(msord, tord);
-  void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev};
+  void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev, &parts};
+  const void *parts_in = parts;
+  void *rargs[] = {&plans_dev, &parts_in, &bpf};
   if (!graph) {
     if ((run.reach_host ? boxes : models) &&
         hipLaunchKernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
+      return DFR_E_DEVICE;
+    if (boxes && hipLaunchKernel(reach_kernel_ptr(), dim3(n), dim3(256), rargs, 0, stream) !=
+                     hipSuccess)
       return DFR_E_DEVICE;
     if (run.reach_host) {
       // the reach boxes the prepass recorded, back to the host (none:
@@ -494,7 +501,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       bg.models = models ? mkernel : nullptr;
       bg.plans_dev = plans_dev;
       if (hipGraphCreate(&bg.graph, 0) != hipSuccess) return DFR_E_DEVICE;
-      hipGraphNode_t mod = nullptr, kern = nullptr;
+      hipGraphNode_t mod = nullptr, box = nullptr, kern = nullptr;
       bool ok = true;
       if (models) {
         hipKernelNodeParams mp;
@@ -504,6 +511,16 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
         mp.blockDim = dim3(64);
         mp.kernelParams = margs;
         ok = hipGraphAddKernelNode(&mod, bg.graph, nullptr, 0, &mp) == hipSuccess;
+      }
+      if (boxes) {
+        hipKernelNodeParams bp;
+        std::memset(&bp, 0, sizeof(bp));
+        bp.func = const_cast<void *>(reach_kernel_ptr());
+        bp.gridDim = dim3(n);
+        bp.blockDim = dim3(256);
+        bp.kernelParams = rargs;
+        ok = ok && hipGraphAddKernelNode(&box, bg.graph, &mod, 1, &bp) == hipSuccess;
+        mod = box;
       }
       TileGeom geom = G;
       int first = 0, nitems = total;

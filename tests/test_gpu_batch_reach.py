@@ -48,6 +48,16 @@ def _frames(order, factor):
 @pytest.mark.parametrize("order,factor", [(0, 1.0), (2, 1.0), (3, 300.0), (5, 30.0), (6, 1.0), (9, 300.0)])
 def test_frames_equal_single_calls(dfr, order, factor, interp):
     print(f"reach order={order} factor={factor} interp={interp}", flush=True)
+    _compare(dfr, order, factor, interp, SHAPE)
+
+
+@pytest.mark.parametrize("shape", [(2200, 3000), (300, 40000), (2049, 257)])
+def test_blocks_of_larger_grids(dfr, shape):
+    print(f"reach shape={shape}", flush=True)
+    _compare(dfr, 3, 30.0, "bilinear", shape)
+
+
+def _compare(dfr, order, factor, interp, SHAPE):
     frames = _frames(order, factor)
     tw = configs.plain().tgt_wcs.copy(crpix=(SHAPE[1] / 2, SHAPE[0] / 2))
     srcs = [torch.from_numpy(s).cuda() for s, _ in frames]
