@@ -166,9 +166,16 @@ __host__ __device__ inline void sip_taylor(const double *__restrict__ c, double 
 // Position model of cell (cx, cy) of the output grid.  SORD: source SIP
 // order at compile time (< 0: any order up to kMaxOrder; the padded
 // coefficients make both give the same model).  TN: highest target SIP order
-// the instance covers (0: a target with SIP gets no model).
+// the instance covers (0: a target with SIP gets no model).  C: the
+// polynomials' coefficients, from the plan or a copy of it in LDS.
+struct SipCoefs {
+  const double *sA, *sB;  // source AP, BP
+  const double *tA, *tB;  // target A, B (TN > 0)
+};
+
 template <int SORD, int TN = 0>
-__host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, CellModel &M) {
+__host__ __device__ inline void cell_model(const FramePlan &P, const SipCoefs &C, int cx, int cy,
+                                           CellModel &M) {
   constexpr int N = SORD >= 0 ? SORD : kMaxOrder;
   const double h = kHalfCell;
 #pragma unroll
@@ -208,7 +215,7 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
       d.c[main] += 1.0;
       return t[0];
     };
-    const double a0 = correct(P.tA, cm_idx(1, 0), du), b0 = correct(P.tB, cm_idx(0, 1), dv);
+    const double a0 = correct(C.tA, cm_idx(1, 0), du), b0 = correct(C.tB, cm_idx(0, 1), dv);
     uc += a0;
     vc += b0;
   }
@@ -269,8 +276,8 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   double sa0 = 0.0, sb0 = 0.0;
   if (N > 0 && P.s_order > 0) {
     double ta[kMaxCoef], tb[kMaxCoef];
-    sip_taylor<N>(P.sA, Uc, Vc, ta);
-    sip_taylor<N>(P.sB, Uc, Vc, tb);
+    sip_taylor<N>(C.sA, Uc, Vc, ta);
+    sip_taylor<N>(C.sB, Uc, Vc, tb);
     sa0 = ta[0];
     sb0 = tb[0];
     // degree 1..3 in (dU, dV): Taylor-model powers of al, be
@@ -375,6 +382,45 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
   M.certified = __builtin_fmax(tx, ty) <= kModelTol ? 1 : 0;
 }
 
+// The coefficients of a frame copied into LDS by one wave (POLYS: 2 without,
+// 4 with the target's).  From the plan the compiler reads them with scalar
+// loads, and as the scalar registers hold few, in small pieces as it goes: 128
+// waits in the order-5 kernel, several us of a wave's time.  From LDS they are
+// vector loads in flight together.  Models of one image, order 5, target with
+// SIP (2048^2): 7.5 -> 5.5 us; without (8192^2): 8.6 -> 8.0; of 64 frames on
+// 8192^2: 195 -> 156.  Not in the launch whose groups make their own models
+// (forward_tile): it measured the same either way.
+template <int POLYS>
+struct LdsCoefs {
+  double c[POLYS][kMaxCoef];
+  float f[2][kMaxCoef];  // the source's scaled FP32 copies (cell_out_of_reach)
+};
+template <int POLYS, class PlanPtr>
+__device__ __forceinline__ SipCoefs stage_coefs(PlanPtr P, LdsCoefs<POLYS> &L) {
+  const int lane = threadIdx.x & 63;
+  if (lane < kMaxCoef) {
+    L.c[0][lane] = P->sA[lane];
+    L.c[1][lane] = P->sB[lane];
+    L.f[0][lane] = P->fsA[lane];
+    L.f[1][lane] = P->fsB[lane];
+    if constexpr (POLYS == 4) {
+      L.c[2][lane] = P->tA[lane];
+      L.c[3][lane] = P->tB[lane];
+    }
+  }
+  // the wave's own LDS accesses are performed in order
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  return SipCoefs{L.c[0], L.c[1], L.c[POLYS - 2], L.c[POLYS - 1]};
+}
+
+// A kernel's first argument, a plan by value, as the memory it is passed in
+// (indexing the argument itself by lane would copy the plan to private memory).
+__device__ __forceinline__ const __attribute__((address_space(4))) FramePlan *plan_argument() {
+  return (const __attribute__((address_space(4))) FramePlan *)__builtin_amdgcn_kernarg_segment_ptr();
+}
+
 // Whether cell (cx, cy) of a target without SIP is certain to be found
 // without a tap in the source by both tests that follow a model (its range
 // grown by 4 px; without a certified model the anchor's test), from far fewer
@@ -386,7 +432,8 @@ __host__ __device__ inline void cell_model(const FramePlan &P, int cx, int cy, C
 // distance of 64 |g| (1 + 2 L) + 12 at the cell's corner, where |g| is at most
 // 1.5 times the centre's: 144 |g| + 12.
 template <int SORD>
-__device__ __forceinline__ bool cell_out_of_reach(const FramePlan &P, int cx, int cy) {
+__device__ __forceinline__ bool cell_out_of_reach(const FramePlan &P,
+                                                  const float (&f)[2][kMaxCoef], int cx, int cy) {
   constexpr int N = SORD >= 0 ? SORD : kMaxOrder;
   const double h = kHalfCell;
   const double *H = P.H;
@@ -411,7 +458,7 @@ __device__ __forceinline__ bool cell_out_of_reach(const FramePlan &P, int cx, in
     float vq = 1.0f, vqd = 0.0f;
 #pragma unroll
     for (int q = 0; p + q <= N; ++q) {
-      const float a = fabsf(P.fsA[tri9(p, q)]), b = fabsf(P.fsB[tri9(p, q)]);
+      const float a = fabsf(f[0][tri9(p, q)]), b = fabsf(f[1][tri9(p, q)]);
       const float m = up * vq;
       sa = fmaf(a, m, sa);
       sb = fmaf(b, m, sb);

@@ -49,11 +49,13 @@ hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp,
 template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, int n,
                                                         CellModel *__restrict__ out) {
+  __shared__ LdsCoefs<(TN > 0 ? 4 : 2)> L;
+  const SipCoefs C = stage_coefs(plan_argument(), L);
   const int i = blockIdx.x * 64 + threadIdx.x;
   if (i >= n) return;
   const int cy = i / ncx, cx = i - cy * ncx;
   CellModel M;
-  cell_model<SORD, TN>(P, cx, cy, M);
+  cell_model<SORD, TN>(P, C, cx, cy, M);
   out[i] = M;
 }
 
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(64) void cell_models_kernel(FramePlan P, int ncx, i
 // per lane as far as the compiler knew, and every coefficient was a vector load
 // (64 frames on 8192^2, order 5: 541 us so and with every cell modelled, 397 us
 // with scalar loads and the cheaper models, 306 us with the test, 200 us since
-// reach_kernel folds the boxes).
+// reach_kernel folds the boxes, 161 us with the coefficients in LDS).
 template <int SORD, int TN>
 __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *__restrict__ plans,
                                                               int ncx, int ncy, int bcols,
@@ -83,14 +85,16 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
   using ConstPlan = const __attribute__((address_space(4))) FramePlan;
   ConstPlan *cp = (ConstPlan *)(plans + frame);
   const FramePlan &P = *(const FramePlan *)cp;
+  __shared__ LdsCoefs<(TN > 0 ? 4 : 2)> L;
+  const SipCoefs C = stage_coefs(cp, L);
   int reach = 0;
   const bool in = cx < ncx && cy < ncy;
   const bool reaches = P.reach != nullptr;  // reach boxes are kept (no target SIP)
-  if (in && TN == 0 && reaches && cell_out_of_reach<SORD>(P, cx, cy)) {
+  if (in && TN == 0 && reaches && cell_out_of_reach<SORD>(P, L.f, cx, cy)) {
     if (out) out[c].certified = kCellOut;
   } else if (in) {
     CellModel M;
-    cell_model<SORD, TN>(P, cx, cy, M);
+    cell_model<SORD, TN>(P, C, cx, cy, M);
     if (out) out[c] = M;  // null: only the reach boxes are wanted
     // can any pixel of the cell have a tap inside the source?  From the
     // model's range over the whole cell, grown by 4 px (more than any tap
@@ -150,7 +154,7 @@ const void *reach_kernel_ptr() { return reinterpret_cast<const void *>(reach_ker
 // target SIP both orders up to 5, or any (padding with zero coefficients is
 // exact, and one instance keeps the library small).  A distorted 2048^2 target,
 // orders 3 and 4, bilinear: 128 us per call when every pixel took the chain
-// from anchors, 34 us with models (7.5 us of it this kernel).
+// from anchors, 26 us with models (5.5 us of it this kernel).
 template <template <int, int> class K>
 static const void *pick_models(int sord, int tord) {
   if (tord > 0) return sord >= 0 && sord <= 5 && tord <= 5 ? K<5, 5>::ptr() : K<-1, kMaxOrder>::ptr();

@@ -230,7 +230,7 @@ __device__ __forceinline__ void tile_cells(const FramePlan &P, const TileGeom &G
     } else if (OWN || P.models) {
       if constexpr (OWN) {
         CellModel M;
-        cell_model<SORD>(P, cx, cy, M);
+        cell_model<SORD>(P, SipCoefs{P.sA, P.sB, P.tA, P.tB}, cx, cy, M);
         sh.cell[tid].model = M;
       } else {
         const CellModel *Mg = P.models + tile_cell_index(G, T, tid);
