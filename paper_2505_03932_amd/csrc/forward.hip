@@ -89,8 +89,7 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
   const SipCoefs C = stage_coefs(cp, L);
   int reach = 0;
   const bool in = cx < ncx && cy < ncy;
-  const bool reaches = P.reach != nullptr;  // reach boxes are kept (no target SIP)
-  if (in && TN == 0 && reaches && cell_out_of_reach<SORD>(P, L.f, cx, cy)) {
+  if (in && TN == 0 && cell_out_of_reach<SORD>(P, L.f, cx, cy)) {
     if (out) out[c].certified = kCellOut;
   } else if (in) {
     CellModel M;
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
     // model's range over the whole cell, grown by 4 px (more than any tap
     // support and the tile kernel's guard); without a model, the anchor's
     // rigorous test with the widest support
-    if (P.src_w <= 0 || P.src_h <= 0 || !reaches) {
+    if (P.src_w <= 0 || P.src_h <= 0 || !parts) {
       reach = 0;
     } else if (!M.certified) {
       Anchor A;
@@ -115,7 +114,7 @@ __global__ __launch_bounds__(64) void cell_models_batch_kernel(const FramePlan *
                yc - ry <= (float)(P.src_h - 1)) ? 1 : 0;
     }
   }
-  if (!reaches) return;
+  if (!parts) return;  // no reach boxes wanted
   // the block's box, for reach_kernel
   const int v0 = wave_max(reach ? kReachBig - cx : 0), v1 = wave_max(reach ? cx + 1 : 0);
   const int v2 = wave_max(reach ? kReachBig - cy : 0), v3 = wave_max(reach ? cy + 1 : 0);

@@ -390,7 +390,9 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   // blocks | per-frame model tables (when used)
   // a target with SIP has no reach boxes: every tile visits every frame
   const int tord = plans[0].t_order;
-  const bool boxes = models && tord == 0;
+  // (nor has a cropped call: its windows are the boxes of an earlier prepass, so
+  // its items end early by their cells' marks alone)
+  const bool boxes = models && tord == 0 && run.crop_items < 0;
   int msord = 0;  // the models' source order
   for (const FramePlan &P : plans) msord = std::max(msord, P.s_order);
   const int ncx = (G.out_w + kCell - 1) / kCell, ncy = (G.out_h + kCell - 1) / kCell;
@@ -452,7 +454,7 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   }
   stage.pending = true;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
-  int4 *parts = reinterpret_cast<int4 *>(dev + pofs);
+  int4 *parts = boxes ? reinterpret_cast<int4 *>(dev + pofs) : nullptr;
   const dim3 mgrid((unsigned)n * (unsigned)bpf);
   const void *mkernel = cell_models_batch_ptr(msord, tord);
   void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev, &parts};

@@ -78,6 +78,8 @@ void reproject_batch(const FramePlan *__restrict__ plans, int first, int total, 
   const FramePlan &P = *(const FramePlan *)((ConstPlan *)(plans + frame));
   const int tile = item - frame * G.n_tiles;
   StoreSink sink;
+  // (also where frames cover all of the grid: without the look at the box the
+  // launch of 24 frames bilinear on 4096^2 took 684 us instead of 606)
   if (tile_out_of_reach<NP>(P, G, tile))
     tile_uncovered<NP>(P, G, tile);  // most of a frame that covers part of the grid
   else
@@ -111,10 +113,7 @@ void reproject_batch_cropped(const FramePlan *__restrict__ plans, int n_frames, 
   const int k = item - P.item0;
   const int tile = (P.tile0[1] + k / P.ntx) * G.tiles_x + P.tile0[0] + k % P.ntx;
   CropSink sink;
-  if (tile_out_of_reach<NP>(P, G, tile))
-    sink.uncovered<NP>(P, G, tile);
-  else
-    forward_tile<INTERP, SORD, NP>(P, G, tile, lds, sh, sink);
+  forward_tile<INTERP, SORD, NP>(P, G, tile, lds, sh, sink);
 }
 
 // Coadd (stacking) of many frames onto one target grid, the paper's
