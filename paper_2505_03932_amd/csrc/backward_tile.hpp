@@ -121,10 +121,14 @@ __device__ __forceinline__ bool tile_anchors(const FramePlan &P, const TileGeom 
         const int ye = min(ya + kCell, min(c.y0 + TH, G.out_h));
         if (xe > xa && ye > ys) {
           const float ux = (float)(xe - 1 - xa), v0 = (float)(ys - ya), v1 = (float)(ye - 1 - ya);
-          const float xl = A.sx0 + fminf(0.0f, A.jx[0] * ux) + fminf(A.jx[1] * v0, A.jx[1] * v1) - A.ex;
-          const float xh = A.sx0 + fmaxf(0.0f, A.jx[0] * ux) + fmaxf(A.jx[1] * v0, A.jx[1] * v1) + A.ex;
-          const float yl = A.sy0 + fminf(0.0f, A.jy[0] * ux) + fminf(A.jy[1] * v0, A.jy[1] * v1) - A.ey;
-          const float yh = A.sy0 + fmaxf(0.0f, A.jy[0] * ux) + fmaxf(A.jy[1] * v0, A.jy[1] * v1) + A.ey;
+          const float xl =
+              A.sx0 + fminf(0.0f, A.jx[0] * ux) + fminf(A.jx[1] * v0, A.jx[1] * v1) - A.ex;
+          const float xh =
+              A.sx0 + fmaxf(0.0f, A.jx[0] * ux) + fmaxf(A.jx[1] * v0, A.jx[1] * v1) + A.ex;
+          const float yl =
+              A.sy0 + fminf(0.0f, A.jy[0] * ux) + fminf(A.jy[1] * v0, A.jy[1] * v1) - A.ey;
+          const float yh =
+              A.sy0 + fmaxf(0.0f, A.jy[0] * ux) + fmaxf(A.jy[1] * v0, A.jy[1] * v1) + A.ey;
           bounded = A.ok && fabsf(xl) < 1.0e7f && fabsf(xh) < 1.0e7f && fabsf(yl) < 1.0e7f &&
                     fabsf(yh) < 1.0e7f;
           if (bounded) {
@@ -629,27 +633,27 @@ void reproject_bwd(FramePlan P, TileGeom G,
                                     gxs[e], gys[e]);
       } else {
 #pragma unroll
-      for (int e = 0; e < kRun; ++e) {
-        gxs[e] = 0.0f;
-        gys[e] = 0.0f;
-        if (!(T.valid & (1u << (k * kRun + e)))) continue;
-        const float g = gr[k][e];
-        if (g == 0.0f) continue;
-        float gx, gy;
-        bool cov;
-        if (use_lds)
-          cov = interp_backward<INTERP, true>(T.abx[k], T.aby[k], T.rx[k][e], T.ry[k][e], W, Hs,
-                                              G.cubic_a, g, fetch_lds, scat_lds, flat, gx, gy);
-        else
-          cov = interp_backward<INTERP, false>(T.abx[k], T.aby[k], T.rx[k][e], T.ry[k][e], W,
-                                               Hs, G.cubic_a, g, fetch_glb, scat_glb, flat, gx,
-                                               gy);
-        if (cov) {
-          gxs[e] = gx;
-          gys[e] = gy;
-          covm |= 1u << e;
+        for (int e = 0; e < kRun; ++e) {
+          gxs[e] = 0.0f;
+          gys[e] = 0.0f;
+          if (!(T.valid & (1u << (k * kRun + e)))) continue;
+          const float g = gr[k][e];
+          if (g == 0.0f) continue;
+          float gx, gy;
+          bool cov;
+          if (use_lds)
+            cov = interp_backward<INTERP, true>(T.abx[k], T.aby[k], T.rx[k][e], T.ry[k][e], W, Hs,
+                                                G.cubic_a, g, fetch_lds, scat_lds, flat, gx, gy);
+          else
+            cov = interp_backward<INTERP, false>(T.abx[k], T.aby[k], T.rx[k][e], T.ry[k][e], W,
+                                                 Hs, G.cubic_a, g, fetch_glb, scat_glb, flat, gx,
+                                                 gy);
+          if (cov) {
+            gxs[e] = gx;
+            gys[e] = gy;
+            covm |= 1u << e;
+          }
         }
-      }
       }
       if constexpr (INTERP != DFR_NEAREST) {
         // the WCS terms of the run's covered pixels, in pixel order
