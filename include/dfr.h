@@ -203,7 +203,9 @@ typedef struct dfr_frame {
  * footprints[i] are device [out_h][out_w] float32 (footprints or any entry
  * of it nullable).  The result of every frame is bit-identical to
  * dfr_reproject of that frame with the same options.  The graph is cached
- * per (n, out shape, interp, orders, tile) and replayed when they repeat. */
+ * per (n, out shape, interp, orders, tile) and replayed when they repeat.
+ * A stream under capture is refused (DFR_E_DEVICE), as by every call that
+ * takes a table of frames. */
 dfr_status dfr_reproject_batch(int32_t n, const dfr_frame *frames, const dfr_wcs *tgt_wcs,
                                int32_t out_h, int32_t out_w, dfr_interp interp,
                                float *const *outs, float *const *footprints,

@@ -287,6 +287,14 @@ std::map<std::pair<int, void *>, Workspace> g_ws;
 
 std::mutex &workspace_mutex() { return g_ws_mutex; }
 
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess)
+    return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 Workspace *workspace(hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
@@ -380,6 +388,11 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
                      const BatchRun &run) {
   const CoaddOut *coadd = run.coadd;
   const int total = (int)plans.size() * G.n_tiles;
+  // A stack call cannot be recorded: the copy of its frame table would read, on
+  // replay, whatever a later call has put into the staging buffer, and a graph
+  // launched into a capturing stream runs at once, on the table of an earlier
+  // call.  Refused before anything is queued.
+  if (capturing(stream)) return DFR_E_DEVICE;
   if (coadd || run.crop_items >= 0 || run.reach_host || total > kBatchItems) graph = false;
   std::lock_guard<std::mutex> lk(g_ws_mutex);
   Workspace *w = workspace(stream);

@@ -86,6 +86,9 @@ struct Workspace {
 };
 
 std::mutex &workspace_mutex();
+// Whether what is queued on `stream` would be recorded into a graph instead of
+// run (also where that cannot be told).
+bool capturing(hipStream_t stream);
 Workspace *workspace(hipStream_t stream);
 // Device scratch of at least `bytes` for the workspace, into *buf:
 // DFR_E_DEVICE if waiting for the stream's earlier work (before replacing a

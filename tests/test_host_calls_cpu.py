@@ -1,0 +1,125 @@
+"""What the library asks of the HIP runtime, call by call, with a recording
+stand-in for the runtime (fake_hip.cpp): no GPU, no kernel runs.  Calls under
+stream capture, allocation failures and failed launches are forced from here.
+
+Each case runs in a process of its own: the stand-in has to be loaded before
+libdfr.so, and torch (whose own HIP runtime would be found first) not at all."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C, importlib.util, math, os, sys
+fake = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+fake.fake_log.restype = C.c_char_p
+sys.modules["torch"] = None
+spec = importlib.util.spec_from_file_location("_lib", sys.argv[2])
+lib = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(lib)
+
+keep = []
+
+def wcs(rot=0.0, ab=0, apbp=0, size=64, eps=1e-7):
+    w = lib.dfr_wcs()
+    w.crpix[:] = [0.5 * (size + 1)] * 2
+    w.crval[:] = [150.0, 2.0]
+    s, r = 8e-4, math.radians(rot)
+    w.cd[:] = [-s * math.cos(r), s * math.sin(r), s * math.sin(r), s * math.cos(r)]
+    for order, names in ((ab, "ab"), (apbp, ("ap", "bp"))):
+        for n in names if order else ():
+            c = (C.c_double * (order + 1) ** 2)()
+            c[2] = eps  # the (0, 2) term
+            keep.append(c)
+            setattr(w, n + "_order", order)
+            setattr(w, n, C.addressof(c))
+    return w
+
+def opts():
+    o = lib.dfr_options()
+    lib.dfr_options_init(o)
+    return o
+
+def names():
+    return [n.decode() for n in fake.fake_log().split()]
+
+IMG = 1 << 20  # an address: no kernel runs, nothing reads it
+STREAM = 4096
+
+def reproject(n=64, out=64, ab=0, apbp=2, rot=0.3):
+    return lib.dfr_reproject(IMG, n, n, n, wcs(rot, 0, apbp, n), wcs(0.0, ab, 0, out), out, out, 1,
+                             IMG, IMG, opts(), STREAM)
+
+def frames(k, n=64, apbp=2):
+    f = (lib.dfr_frame * k)()
+    for i in range(k):
+        f[i].src, f[i].h, f[i].w, f[i].pitch, f[i].wcs = IMG, n, n, n, wcs(0.3, 0, apbp, n)
+    return f
+
+def pointers(k):
+    return (C.c_void_p * k)(*[IMG] * k)
+
+def stack(kind, k=3, out=64, ab=0):
+    tw = wcs(0.0, ab, 0, out)
+    if kind == "batch":
+        return lib.dfr_reproject_batch(k, frames(k), tw, out, out, 1, pointers(k), None, opts(), STREAM)
+    if kind == "coadd":
+        return lib.dfr_coadd_batch(k, frames(k), tw, out, out, 1, IMG, IMG, None, 0, opts(), STREAM)
+    boxes = (C.c_int32 * (4 * k))(*[0, 0, out, out] * k)
+    if kind == "boxes":
+        return lib.dfr_batch_boxes(k, frames(k), tw, out, out, 1, opts(), STREAM,
+                                   C.cast(boxes, C.c_void_p))
+    return lib.dfr_reproject_batch_cropped(k, frames(k), tw, out, out, 1,
+                                           C.cast(boxes, C.c_void_p), pointers(k), None, opts(), STREAM)
+
+OK, DEVICE, NOMEM = 0, 5, 6
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "fake_hip.cpp")], check=True)
+    return so
+
+
+def run(fake, body):
+    r = subprocess.run([sys.executable, "-c", PRELUDE + body, fake,
+                        os.path.join(ROOT, "paper_2505_03932_amd", "_lib.py")],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_the_stand_in_is_the_one_bound(fake):
+    run(fake, """
+assert reproject() == OK
+assert len(names()) == 1 and "reproject_small" in names()[0], names()
+assert reproject(out=2048) == OK
+assert "cell_models_kernel" in names()[1] and "reproject_tiles" in names()[2], names()
+""")
+
+
+@pytest.mark.parametrize("kind", ["batch", "coadd", "boxes", "cropped"])
+def test_stack_calls_are_refused_under_capture(fake, kind):
+    """Their frame table is copied from a staging buffer that later calls
+    refill, and a graph launched into a capturing stream runs at once, with
+    whatever table an earlier call left: refused before anything is queued,
+    and the stream's later calls work."""
+    run(fake, f'''
+for _ in range(5):
+    assert stack({kind!r}) == OK
+fake.fake_set_capturing(1)
+before = (fake.fake_copies(), fake.fake_graph_launches(), len(names()))
+for _ in range(5):
+    assert stack({kind!r}) == DEVICE
+assert before == (fake.fake_copies(), fake.fake_graph_launches(), len(names()))
+assert fake.fake_last_error() == 0
+fake.fake_set_capturing(0)
+for _ in range(5):
+    assert stack({kind!r}) == OK
+''')
