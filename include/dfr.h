@@ -122,7 +122,10 @@ void dfr_options_init(dfr_options *opt);
  *              src_w is 0: then every output pixel is uncovered)
  *   out        device, [out_h][out_w] float32 (may be NULL when out_h*out_w=0)
  *   footprint  device, [out_h][out_w] float32, nullable
- *   opt        host, nullable (defaults)                                      */
+ *   opt        host, nullable (defaults)
+ * On a stream under capture a target with SIP takes the chain from anchors
+ * (the results of DFR_PREC_F32_ANCHOR, within 2e-5 px), which needs none of the
+ * stream's scratch, so the graph stays valid whatever is called later. */
 dfr_status dfr_reproject(const float *src, int32_t src_h, int32_t src_w, int64_t src_pitch,
                          const dfr_wcs *src_wcs, const dfr_wcs *tgt_wcs,
                          int32_t out_h, int32_t out_w, dfr_interp interp,

@@ -42,8 +42,9 @@ bool is_f32(const dfr_options &o) {
 // first (default precision; the table lives in the stream's workspace, so the
 // caller holds workspace_mutex() from here until every launch reading it is
 // queued).  A target with SIP does without the table (the anchored chain)
-// where it cannot be had: no memory, or a stream being captured, where the
-// workspace cannot grow.
+// where there is no memory for it, and always on a stream being captured: the
+// graph would keep the table's address, which a later call that grows the
+// workspace frees, and its replays would race on it with calls on this stream.
 dfr_status models_for(FramePlan &P, int32_t out_h, int32_t out_w, const dfr_options &o,
                       hipStream_t st) {
   P.models = nullptr;
@@ -51,11 +52,7 @@ dfr_status models_for(FramePlan &P, int32_t out_h, int32_t out_w, const dfr_opti
   const int ncx = (out_w + kCell - 1) / kCell, ncy = (out_h + kCell - 1) / kCell;
   const size_t bytes = (size_t)ncx * ncy * sizeof(CellModel);
   Workspace *w = workspace(st);
-  if (P.t_order > 0 && w && w->cap < bytes) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) return DFR_E_DEVICE;
-    if (cap != hipStreamCaptureStatusNone) return DFR_OK;
-  }
+  if (P.t_order > 0 && capturing(st)) return DFR_OK;
   void *buf = nullptr;
   dfr_status s = workspace_buffer(w, bytes, &buf);
   if (s == DFR_E_NOMEM && P.t_order > 0) return DFR_OK;

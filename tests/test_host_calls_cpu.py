@@ -123,3 +123,19 @@ fake.fake_set_capturing(0)
 for _ in range(5):
     assert stack({kind!r}) == OK
 ''')
+
+
+def test_captured_target_with_sip_keeps_no_scratch(fake):
+    """Whatever the stream's workspace already holds, a captured call of a
+    target with SIP records the tile kernel alone, on the anchored chain: no
+    table whose address the graph would keep."""
+    run(fake, '''
+for out in (64, 2048):
+    assert reproject(out=out, ab=2) == OK  # the stream's workspace exists now
+    assert "cell_models_kernel" in names()[-2] and "reproject_tiles" in names()[-1], names()
+    fake.fake_set_capturing(1)
+    n = len(names())
+    assert reproject(out=out, ab=2) == OK
+    assert len(names()) == n + 1 and "reproject_tiles" in names()[-1], names()
+    fake.fake_set_capturing(0)
+''')
