@@ -173,7 +173,9 @@ typedef struct dfr_plan dfr_plan;
  * pointer is not needed yet: src_h and src_w fix the shape.  Errors as for
  * dfr_reproject; only the FP32 forms (DFR_PREC_F32, DFR_PREC_F32_ANCHOR)
  * have plans (DFR_E_UNSUPPORTED otherwise), debug positions are refused
- * (DFR_E_ARG), DFR_E_NOMEM when the model table cannot be allocated.
+ * (DFR_E_ARG), DFR_E_NOMEM when the model table cannot be allocated (a
+ * target with SIP: the plan then takes the chain from anchors instead, as one
+ * created while `stream` is under capture does).
  *   plan  host, out: the new plan (NULL on error)                         */
 dfr_status dfr_plan_create(int32_t src_h, int32_t src_w, const dfr_wcs *src_wcs,
                            const dfr_wcs *tgt_wcs, int32_t out_h, int32_t out_w,

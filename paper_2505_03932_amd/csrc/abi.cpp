@@ -479,7 +479,11 @@ dfr_status dfr_plan_create(int32_t src_h, int32_t src_w, const dfr_wcs *src_wcs,
   const int tile = choose_tile(pl->P, out_h, out_w, (int)interp, o.tile, false);
   make_geom(pl->P, out_h, out_w, (int)interp, tile, o, pl->G, ts);
   pl->np = ts.np;
-  if (o.precision == DFR_PREC_F32 && out_h > 0 && out_w > 0) {
+  // A target with SIP has models unless they cannot be had now: no memory, or
+  // `stream` under capture, where an allocation ends the capture and the prepass
+  // would only be recorded.
+  if (o.precision == DFR_PREC_F32 && out_h > 0 && out_w > 0 &&
+      !(pl->P.t_order > 0 && capturing(reinterpret_cast<hipStream_t>(stream)))) {
     const int ncx = (out_w + kCell - 1) / kCell, ncy = (out_h + kCell - 1) / kCell;
     if (hipMalloc(&pl->models, (size_t)ncx * ncy * sizeof(CellModel)) != hipSuccess) {
       pl->models = nullptr;
@@ -487,7 +491,7 @@ dfr_status dfr_plan_create(int32_t src_h, int32_t src_w, const dfr_wcs *src_wcs,
         delete pl;
         return DFR_E_NOMEM;
       }
-      (void)hipGetLastError();  // a target with SIP does without: the anchored chain
+      (void)hipGetLastError();
     }
     pl->P.models = pl->models;
     if (pl->models && launch_cell_models(pl->P, ncx, ncy, pl->models,

@@ -52,12 +52,12 @@ hipError_t hipGetDevice(int *d) {
   return 0;
 }
 hipError_t hipMalloc(void **p, size_t n) {
+  ++g_mallocs;  // requests, granted or not
   if (g_capturing) return done(900);
   if (g_fail_malloc > 0) {
     --g_fail_malloc;
     return done(2);
   }
-  ++g_mallocs;
   *p = std::malloc(n);
   return 0;
 }
@@ -66,8 +66,8 @@ hipError_t hipFree(void *p) {
   return 0;
 }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
-  if (g_capturing) return done(900);
   ++g_host_mallocs;
+  if (g_capturing) return done(900);
   *p = std::malloc(n);
   return 0;
 }

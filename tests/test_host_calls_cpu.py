@@ -139,3 +139,28 @@ for out in (64, 2048):
     assert len(names()) == n + 1 and "reproject_tiles" in names()[-1], names()
     fake.fake_set_capturing(0)
 ''')
+
+
+def plan(ab):
+    return f"""
+def plan(out=64):
+    return lib.dfr_plan_create(64, 64, wcs(0.3, 0, 2), wcs(0.0, {ab}, 0, out), out, out, 1, opts(), STREAM)
+"""
+
+
+def test_plan_of_a_target_with_sip_created_under_capture(fake):
+    """Such a plan needs no memory of its own (the anchored chain): none is
+    asked for, which would end the capture, and no model kernel is recorded,
+    which would leave the plan without models until a replay."""
+    run(fake, plan(ab=2) + '''
+fake.fake_set_capturing(1)
+s, h = plan()
+assert s == OK and names() == [] and fake.fake_mallocs() == 0 and fake.fake_last_error() == 0
+assert lib.dfr_plan_execute(h, IMG, 64, IMG, None, STREAM) == OK
+assert len(names()) == 1 and "reproject_tiles" in names()[0], names()
+fake.fake_set_capturing(0)
+assert lib.dfr_plan_destroy(h) == OK
+s, h = plan()
+assert s == OK and "cell_models_kernel" in names()[1] and fake.fake_mallocs() == 1
+assert lib.dfr_plan_destroy(h) == OK
+''')
