@@ -321,6 +321,9 @@ dfr_status workspace_buffer(Workspace *w, size_t bytes, void **buf) {
   }
   size_t cap = std::max<size_t>(bytes + bytes / 4, 1 << 20);
   if (hipMalloc(&w->buf, cap) != hipSuccess) {
+    // (taken here: it would stay the thread's last error, and a caller that does
+    // without the memory would find it after its next launch)
+    (void)hipGetLastError();
     w->buf = nullptr;
     return DFR_E_NOMEM;
   }
@@ -419,7 +422,6 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   dfr_status ws = workspace_buffer(w, mofs + mbytes, &wsbuf);
   if (ws == DFR_E_NOMEM && tord > 0 && mbytes) {
     // a target with SIP does without the tables: the anchored chain
-    (void)hipGetLastError();
     models = false;
     mbytes = 0;
     ws = workspace_buffer(w, mofs, &wsbuf);

@@ -164,3 +164,21 @@ s, h = plan()
 assert s == OK and "cell_models_kernel" in names()[1] and fake.fake_mallocs() == 1
 assert lib.dfr_plan_destroy(h) == OK
 ''')
+
+
+@pytest.mark.parametrize("kind", ["single", "batch", "coadd"])
+def test_target_with_sip_without_memory_for_models(fake, kind):
+    """No memory for the table: the anchored chain runs, and the runtime's
+    out-of-memory error, which the next check of a launch would take for its
+    own, is not left behind."""
+    run(fake, f'''
+call = lambda ab=2: reproject(out=2048, ab=ab) if {kind!r} == "single" else stack({kind!r}, out=2048, ab=ab)
+fake.fake_fail_malloc(1)
+assert call() == OK
+assert not any("cell_models" in n for n in names()), names()
+assert fake.fake_last_error() == 0
+fake.fake_fail_malloc(1)
+assert lib.dfr_release() == OK
+assert call(ab=0) == NOMEM  # a target without SIP has no other form
+assert fake.fake_last_error() == 0 and call(ab=0) == OK
+''')
