@@ -102,7 +102,7 @@ hipError_t launch_bwd_prepare(const FramePlan &P, const TileGeom &G, int interp,
   void *args[] = {&plan, &ncx, &ncells, &support, &nab, &anchors,
                   &grad_out, &n, &q, &nq, &gmax, &gmax_next};
   const void *k = P.t_order > 0 ? prepare_pick<true>(P.s_order) : prepare_pick<false>(P.s_order);
-  return hipLaunchKernel(k, dim3(nab + blocks), dim3(256), args, 0, stream);
+  return launch_kernel(k, dim3(nab + blocks), dim3(256), args, 0, stream);
 }
 
 // Column c of the partials ([ns][n_blocks], column-major), summed by one

@@ -28,8 +28,8 @@ const void *coadd_kernel_ptr(int interp, int np, int sord) {
 static hipError_t launch_items(const void *kernel, int total, int &first, void **args, size_t lds,
                                hipStream_t stream) {
   for (first = 0; first < total; first += kBatchItems) {
-    const hipError_t e = hipLaunchKernel(kernel, dim3(std::min(total - first, kBatchItems)),
-                                         dim3(kThreads), args, lds, stream);
+    const hipError_t e = launch_kernel(kernel, dim3(std::min(total - first, kBatchItems)),
+                                       dim3(kThreads), args, lds, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -28,8 +28,8 @@ hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int inter
   FramePlan plan = P;
   TileGeom geom = G;
   void *args[] = {&plan, &geom};
-  return hipLaunchKernel(k, dim3(G.n_tiles), dim3(kThreads), args,
-                         (size_t)G.lds_cap * sizeof(float), stream);
+  return launch_kernel(k, dim3(G.n_tiles), dim3(kThreads), args,
+                       (size_t)G.lds_cap * sizeof(float), stream);
 }
 
 hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp, int np,
@@ -185,8 +185,8 @@ hipError_t launch_cell_models(const FramePlan &P, int ncx, int ncy, CellModel *o
   if (n <= 0) return hipSuccess;
   FramePlan plan = P;
   void *args[] = {&plan, &ncx, &n, &out};
-  return hipLaunchKernel(pick_models<ModelsK>(P.s_order, P.t_order), dim3((n + 63) / 64), dim3(64),
-                         args, 0, stream);
+  return launch_kernel(pick_models<ModelsK>(P.s_order, P.t_order), dim3((n + 63) / 64), dim3(64),
+                       args, 0, stream);
 }
 
 // ------------------------------------------------------ FP64 comparison forms

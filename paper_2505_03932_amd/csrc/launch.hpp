@@ -72,6 +72,15 @@ struct TrigPlan {
   double scrval[2];  // source (RA, Dec) in radians
 };
 
+// Launch a kernel by its address.  A failure is returned and also taken from the
+// runtime, whose last error would otherwise fail the next checked launch.
+inline hipError_t launch_kernel(const void *kernel, dim3 grid, dim3 block, void **args, size_t lds,
+                                hipStream_t stream) {
+  const hipError_t e = hipLaunchKernel(kernel, grid, block, args, lds, stream);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp, int np,
                               hipStream_t stream);
 // Whether a call with cell models takes the one-launch form for few tiles

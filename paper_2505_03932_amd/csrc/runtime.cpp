@@ -477,10 +477,10 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   void *rargs[] = {&plans_dev, &parts_in, &bpf};
   if (!graph) {
     if ((run.reach_host ? boxes : models) &&
-        hipLaunchKernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
+        launch_kernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
-    if (boxes && hipLaunchKernel(reach_kernel_ptr(), dim3(n), dim3(256), rargs, 0, stream) !=
-                     hipSuccess)
+    if (boxes &&
+        launch_kernel(reach_kernel_ptr(), dim3(n), dim3(256), rargs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
     if (run.reach_host) {
       // the reach boxes the prepass recorded, back to the host (none:

@@ -15,7 +15,8 @@ struct dim3_ {
   unsigned x, y, z;
 };
 
-static int g_last = 0, g_capturing = 0, g_fail_malloc = 0, g_fail_launch = 0;
+static int g_last = 0, g_capturing = 0, g_fail_malloc = 0, g_fail_launch = 0,
+           g_skip_launches = 0;
 static int g_mallocs = 0, g_host_mallocs = 0, g_copies = 0, g_graph_launches = 0;
 static std::map<const void *, std::string> g_names;
 static std::string g_log;  // kernels launched, one name a line
@@ -27,13 +28,14 @@ static hipError_t done(int e) {
 
 // ---- the tests' controls
 void fake_reset() {
-  g_last = g_capturing = g_fail_malloc = g_fail_launch = 0;
+  g_last = g_capturing = g_fail_malloc = g_fail_launch = g_skip_launches = 0;
   g_mallocs = g_host_mallocs = g_copies = g_graph_launches = 0;
   g_log.clear();
 }
 void fake_set_capturing(int on) { g_capturing = on; }
 void fake_fail_malloc(int n) { g_fail_malloc = n; }  // the next n device allocations fail
-void fake_fail_launch(int n) { g_fail_launch = n; }
+void fake_fail_launch(int n) { g_fail_launch = n; }  // the next n launches, after skipped ones
+void fake_skip_launches(int n) { g_skip_launches = n; }
 int fake_mallocs() { return g_mallocs; }
 int fake_host_mallocs() { return g_host_mallocs; }
 int fake_copies() { return g_copies; }
@@ -106,7 +108,9 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
   return 0;
 }
 hipError_t hipLaunchKernel(const void *f, dim3_, dim3_, void **, size_t, void *) {
-  if (g_fail_launch > 0) {
+  if (g_skip_launches > 0) {
+    --g_skip_launches;
+  } else if (g_fail_launch > 0) {
     --g_fail_launch;
     return done(9);
   }

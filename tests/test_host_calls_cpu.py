@@ -182,3 +182,25 @@ assert lib.dfr_release() == OK
 assert call(ab=0) == NOMEM  # a target without SIP has no other form
 assert fake.fake_last_error() == 0 and call(ab=0) == OK
 ''')
+
+
+@pytest.mark.parametrize("call", ["reproject()", "reproject(out=2048)", "reproject(out=2048, ab=2)",
+                                  "stack('boxes')", "stack('cropped')", "backward()"])
+@pytest.mark.parametrize("launch", [0, 1, 2])
+def test_a_failed_launch_fails_its_own_call_only(fake, call, launch):
+    """Whichever of a call's launches fails, the call says so and the next
+    check of a launch, this library's or another's, does not find it again."""
+    run(fake, f'''
+def backward():
+    return lib.dfr_reproject_backward(IMG, 64, 64, 64, wcs(0.3, 0, 2), wcs(), 64, 64, 1, IMG, IMG, IMG,
+                                      opts(), STREAM)
+assert {call} == OK
+before = len(names())
+assert {call} == OK
+if len(names()) - before > {launch}:
+    fake.fake_skip_launches({launch})
+    fake.fake_fail_launch(1)
+    assert {call} == DEVICE
+    assert fake.fake_last_error() == 0
+    assert {call} == OK
+''')
