@@ -336,7 +336,7 @@ __device__ __forceinline__ void interior_backward(int ox, int oy, float rx, floa
   tap_origin<INTERP>(ry, oy, j0, s);
   const int base = __umul24(j0, flat.pitch()) + i0;
   if constexpr (INTERP == DFR_NEAREST) {
-    flat.add_scaled(base, flat.scaled(g));
+    flat.add_nearest(base, flat.scaled(g));
     gx = gy = 0.0f;
   } else {
     float wx[4], wy[4], dx[4], dy[4];
@@ -498,6 +498,13 @@ struct BwdFlat {
   __device__ void add_scaled(int idx, float y) const {
     if constexpr (SRC)
       atomicAdd(&qacc[idx], (unsigned long long)(long long)(int)rintf(y));
+  }
+  // Nearest, y = g 2^Q: a gradient that is not finite gives the integer of the
+  // general path, so it too does not depend on the tile a pixel falls into.
+  __device__ void add_nearest(int idx, float y) const {
+    if constexpr (SRC)
+      atomicAdd(&qacc[idx], fabsf(y) < 0x1p31f ? (unsigned long long)(long long)(int)rintf(y)
+                                               : det_quant(y));
   }
 };
 

@@ -74,3 +74,22 @@ def test_tile_shapes_mix_interior_and_edge_tiles(dfr, interp):
         assert torch.equal(gs, ref[0])
         assert torch.allclose(gw, ref[1], rtol=1e-4, atol=1e-5 * float(ref[1].abs().max()))
     assert float(ref[0].abs().max()) > 0
+
+
+def test_nearest_nan_gradient_on_any_tile(dfr):
+    """The adjoint's integers do not depend on the tile shape, of a gradient
+    that is not finite neither: interior and edge tiles form the same ones."""
+    c = configs.grad(size=150)
+    src = torch.from_numpy(c.src).cuda()
+    shape = (260, 300)
+    tw = c.tgt_wcs.copy(crpix=(c.tgt_wcs.crpix[0] + 70, c.tgt_wcs.crpix[1] + 60))
+    g = torch.randn(shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(9))
+    g[::9, ::7] = float("nan")
+    ref = None
+    for tile in (1, 2, 4, 5, 8, 10):
+        print(f"nearest NaN gradient tile={tile}", flush=True)
+        gs, _ = dfr.reproject_backward(src, c.src_wcs, tw, shape, "nearest", g, tile=tile)
+        ref = gs if ref is None else ref
+        assert torch.equal(gs, ref)
+    clean = dfr.reproject_backward(src, c.src_wcs, tw, shape, "nearest", g.nan_to_num(0.0))[0]
+    assert 0 < (ref != clean).sum() < ref.numel() // 20
