@@ -93,3 +93,33 @@ def test_nearest_nan_gradient_on_any_tile(dfr):
         assert torch.equal(gs, ref)
     clean = dfr.reproject_backward(src, c.src_wcs, tw, shape, "nearest", g.nan_to_num(0.0))[0]
     assert 0 < (ref != clean).sum() < ref.numel() // 20
+
+
+@pytest.mark.parametrize("want_src", [True, False])
+def test_masked_bicubic_gradient_is_passed_over(dfr, want_src):
+    """Waves whose output gradient is all zero do no tap work: a call without
+    any takes under three quarters of a full one (0.6 where they are passed
+    over, 0.9 where they are not), and nothing comes of it."""
+    c = configs.grad(size=2048)
+    src = torch.from_numpy(c.src).cuda()
+    g = torch.randn(c.out_shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+
+    def best(grad):
+        t = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                out = dfr.reproject_backward(src, c.src_wcs, c.tgt_wcs, c.out_shape, "bicubic", grad,
+                                             want_src=want_src)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t), out
+
+    print(f"masked gradient want_src={want_src}", flush=True)
+    full, _ = best(g)
+    none, (gs, gw) = best(torch.zeros_like(g))
+    print("full, none (us)", 50 * full, 50 * none)
+    assert none < 0.75 * full
+    assert (gs is None or not gs.any()) and not gw.any()
