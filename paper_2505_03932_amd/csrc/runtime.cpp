@@ -362,6 +362,47 @@ void destroy_graphs(Workspace &w) {
 
 }  // namespace
 
+namespace {
+
+dfr_status staging_wait(StagingRing &r, int k) {
+  if (r.pending[k] && hipEventSynchronize(r.copied[k]) != hipSuccess) return DFR_E_DEVICE;
+  r.pending[k] = false;
+  return DFR_OK;
+}
+
+// The ring's next slot, of at least `bytes` bytes and not read by a copy any more.
+dfr_status staging_slot(StagingRing &r, size_t bytes, void **buf, int *slot) {
+  for (hipEvent_t &e : r.copied)
+    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+      e = nullptr;
+      return DFR_E_DEVICE;
+    }
+  const int k = r.next;
+  dfr_status s = staging_wait(r, k);
+  if (s != DFR_OK) return s;
+  if (r.slot < bytes) {
+    for (int i = 0; i < kStagings; ++i)
+      if ((s = staging_wait(r, i)) != DFR_OK) return s;
+    if (r.buf) (void)hipHostFree(r.buf);
+    r.buf = nullptr;
+    r.slot = 0;
+    void *mem = nullptr;
+    const size_t size = (bytes + 255) & ~(size_t)255;
+    if (hipHostMalloc(&mem, kStagings * size, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return DFR_E_NOMEM;
+    }
+    r.buf = static_cast<char *>(mem);
+    r.slot = size;
+  }
+  r.next = (k + 1) % kStagings;
+  *buf = r.buf + (size_t)k * r.slot;
+  *slot = k;
+  return DFR_OK;
+}
+
+}  // namespace
+
 void release_workspaces() {
   std::lock_guard<std::mutex> lk(g_ws_mutex);
   int dev = 0;
@@ -376,10 +417,9 @@ void release_workspaces() {
     destroy_graphs(w);
     if (w.buf) (void)hipFree(w.buf);
     if (w.ctl) (void)hipFree(w.ctl);
-    for (Staging &g : w.staging) {
-      if (g.buf) (void)hipHostFree(g.buf);
-      if (g.copied) (void)hipEventDestroy(g.copied);
-    }
+    if (w.staging.buf) (void)hipHostFree(w.staging.buf);
+    for (hipEvent_t e : w.staging.copied)
+      if (e) (void)hipEventDestroy(e);
     it = g_ws.erase(it);
   }
 }
@@ -431,43 +471,27 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   int32_t *reach = reinterpret_cast<int32_t *>(dev);
   FramePlan *plans_dev = reinterpret_cast<FramePlan *>(dev + tofs);
   CellModel *models_dev = mbytes ? reinterpret_cast<CellModel *>(dev + mofs) : nullptr;
-  // the next staging buffer, once its last copy has ended: with one buffer a
+  // the next staging slot, once its last copy has ended: with one slot a
   // call would wait here for the whole previous batch on the stream (its copy
   // is ordered behind that batch's kernels), so the GPU ran dry between calls
-  Staging &stage = w->staging[w->next_staging];
-  w->next_staging = (w->next_staging + 1) % kStagings;
-  if (stage.pending) {
-    if (hipEventSynchronize(stage.copied) != hipSuccess) return DFR_E_DEVICE;
-    stage.pending = false;
-  }
-  if (stage.cap < tofs + table) {
-    if (stage.buf) (void)hipHostFree(stage.buf);
-    stage.buf = nullptr;
-    stage.cap = 0;
-    if (hipHostMalloc(&stage.buf, tofs + table, hipHostMallocDefault) != hipSuccess) {
-      stage.buf = nullptr;
-      return DFR_E_NOMEM;
-    }
-    stage.cap = tofs + table;
-  }
-  if (!stage.copied && hipEventCreateWithFlags(&stage.copied, hipEventDisableTiming) != hipSuccess)
-    return DFR_E_DEVICE;
-  std::memset(stage.buf, 0, tofs);
-  FramePlan *host_plans =
-      reinterpret_cast<FramePlan *>(static_cast<char *>(stage.buf) + tofs);
+  void *stage = nullptr;
+  int slot = 0;
+  if ((ws = staging_slot(w->staging, tofs + table, &stage, &slot)) != DFR_OK) return ws;
+  std::memset(stage, 0, tofs);
+  FramePlan *host_plans = reinterpret_cast<FramePlan *>(static_cast<char *>(stage) + tofs);
   std::memcpy(host_plans, plans.data(), table);
   for (int i = 0; i < n; ++i) {
     host_plans[i].models = mbytes ? models_dev + i * ncells : nullptr;
     host_plans[i].reach = boxes ? reach + 4 * i : nullptr;
   }
   // (the reach boxes' place goes with it, zero; the prepass writes them)
-  if (hipMemcpyAsync(dev, stage.buf, tofs + table, hipMemcpyHostToDevice, stream) != hipSuccess)
+  if (hipMemcpyAsync(dev, stage, tofs + table, hipMemcpyHostToDevice, stream) != hipSuccess)
     return DFR_E_DEVICE;
-  if (hipEventRecord(stage.copied, stream) != hipSuccess) {
+  if (hipEventRecord(w->staging.copied[slot], stream) != hipSuccess) {
     (void)hipStreamSynchronize(stream);  // the copy may still read the buffer
     return DFR_E_DEVICE;
   }
-  stage.pending = true;
+  w->staging.pending[slot] = true;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
   int4 *parts = boxes ? reinterpret_cast<int4 *>(dev + pofs) : nullptr;
   const dim3 mgrid((unsigned)n * (unsigned)bpf);

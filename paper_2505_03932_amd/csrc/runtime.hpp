@@ -62,23 +62,27 @@ struct BatchGraph {
   hipGraphExec_t exec;
 };
 
-// Pinned host memory a batch's frame table is copied from; `copied` is
-// recorded after that copy.
-struct Staging {
-  void *buf = nullptr;
-  size_t cap = 0;
-  hipEvent_t copied = nullptr;
-  bool pending = false;
-};
+// Pinned host memory the frame tables of batches are copied from, in slots
+// used in turn; a slot's event is recorded after its copy.  One allocation for
+// all slots, at the first batch or the first larger one: allocated slot by slot,
+// each of the first four calls paid for pinned memory and an event (six small
+// frames on 256^2, us per call: 196, 186, 176, 190, then 150, that way; 190,
+// 152, 149, 148 so).
 constexpr int kStagings = 4;  // batches that can be queued on a stream before a call waits
+struct StagingRing {
+  char *buf = nullptr;
+  size_t slot = 0;  // bytes of one
+  hipEvent_t copied[kStagings] = {};
+  bool pending[kStagings] = {};
+  int next = 0;
+};
 
 struct Workspace {
   int device = -1;
   hipStream_t stream = nullptr;
   void *buf = nullptr;  // device scratch
   size_t cap = 0;
-  Staging staging[kStagings];
-  int next_staging = 0;
+  StagingRing staging;
   std::vector<BatchGraph> graphs;
   int *ctl = nullptr;      // backward control words: max|g| bits in two alternating slots
   int ctl_slot = 0;        // the slot the next backward call uses (zero)

@@ -204,3 +204,15 @@ if len(names()) - before > {launch}:
     assert fake.fake_last_error() == 0
     assert {call} == OK
 ''')
+
+
+def test_staging_is_allocated_once_a_size(fake):
+    """Pinned memory is asked for by the first stack call on a stream and by
+    the first larger one, not by the calls that follow."""
+    run(fake, '''
+asked = []
+for k in [3] * 6 + [40] * 6 + [3] * 3 + [40]:
+    assert stack("coadd", k) == OK
+    asked.append(fake.fake_host_mallocs())
+assert asked == [1] * 6 + [2] * 10, asked
+''')
