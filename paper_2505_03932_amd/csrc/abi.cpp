@@ -95,13 +95,14 @@ std::string batch_key(const std::vector<FramePlan> &plans, int32_t out_h, int32_
 }
 
 // Geometry for a batch with tile `t`: the LDS budget covers the largest
-// estimated source box over the frames.
+// estimated source box over the frames (`known`: the first one's estimates).
 void batch_geom(const std::vector<FramePlan> &plans, int32_t out_h, int32_t out_w, int interp,
-                int t, const dfr_options &o, TileGeom &G, int &np) {
+                int t, const dfr_options &o, TileGeom &G, int &np, LdsNeeds &known) {
   TileShape ts;
-  make_geom(plans[0], out_h, out_w, interp, t, o, G, ts);
-  int64_t need = 0;
-  for (auto &P : plans) need = std::max<int64_t>(need, estimate_lds_floats(P, out_h, out_w, ts, interp));
+  make_geom(plans[0], out_h, out_w, interp, t, o, G, ts, known);
+  int64_t need = lds_need(plans[0], out_h, out_w, interp, t, known);
+  for (size_t i = 1; i < plans.size(); ++i)
+    need = std::max<int64_t>(need, estimate_lds_floats(plans[i], out_h, out_w, ts, interp));
   G.lds_cap = need <= kLdsMaxFloats ? (int32_t)need : 0;
   np = ts.np;
 }
@@ -155,8 +156,11 @@ dfr_status prepare_batch(int32_t n, const dfr_frame *frames, const dfr_wcs *tgt_
     std::lock_guard<std::mutex> lk(tune_mutex_for_batch());
     tile = tuned_tile(batch_key(plans, out_h, out_w, interp, max_sord));
   }
-  if (tile == 0) tile = stack ? kCoaddTile : choose_tile(plans[0], out_h, out_w, interp, 0, true, 1, 0, n);
-  batch_geom(plans, out_h, out_w, interp, tile, o, G, np);
+  LdsNeeds known;
+  if (tile == 0)
+    tile = stack ? kCoaddTile
+                 : choose_tile(plans[0], out_h, out_w, interp, 0, true, known, 1, 0, n);
+  batch_geom(plans, out_h, out_w, interp, tile, o, G, np, known);
   return DFR_OK;
 }
 
@@ -250,7 +254,8 @@ dfr_status dfr_reproject(const float *src, int32_t src_h, int32_t src_w, int64_t
     build_trig_plan(*src_wcs, *tgt_wcs, T);
     TileGeom G;
     TileShape ts;
-    make_geom(P, out_h, out_w, (int)interp, kDefaultTile, o, G, ts);
+    LdsNeeds known;
+    make_geom(P, out_h, out_w, (int)interp, kDefaultTile, o, G, ts, known);
     e = launch_forward_f64(P, T, G, (int)interp, o.precision == DFR_PREC_TRIG_F64, st);
   }
   return e == hipSuccess ? DFR_OK : DFR_E_DEVICE;
@@ -302,7 +307,8 @@ dfr_status dfr_reproject_noalloc(const float *src, int32_t src_h, int32_t src_w,
     build_trig_plan(*src_wcs, *tgt_wcs, T);
     TileGeom G;
     TileShape ts;
-    make_geom(P, out_h, out_w, (int)interp, kDefaultTile, o, G, ts);
+    LdsNeeds known;
+    make_geom(P, out_h, out_w, (int)interp, kDefaultTile, o, G, ts, known);
     e = launch_forward_f64(P, T, G, (int)interp, o.precision == DFR_PREC_TRIG_F64, st);
   }
   return e == hipSuccess ? DFR_OK : DFR_E_DEVICE;
@@ -345,7 +351,8 @@ dfr_status dfr_coadd_batch(int32_t n, const dfr_frame *frames, const dfr_wcs *tg
     FramePlan P;
     build_plan(nullptr, 0, 0, 0, *tgt_wcs, *tgt_wcs, out_h, out_w, nullptr, nullptr, P);
     TileShape ts;
-    make_geom(P, out_h, out_w, (int)interp, o.tile ? o.tile : kCoaddTile, o, G, ts);
+    LdsNeeds known;
+    make_geom(P, out_h, out_w, (int)interp, o.tile ? o.tile : kCoaddTile, o, G, ts, known);
     G.lds_cap = 0;
     return launch_coadd_f32(nullptr, 0, 0, G, (int)interp, ts.np, C, st) == hipSuccess
                ? DFR_OK
@@ -476,8 +483,9 @@ dfr_status dfr_plan_create(int32_t src_h, int32_t src_w, const dfr_wcs *src_wcs,
   build_plan(nullptr, src_h, src_w, src_w, *src_wcs, *tgt_wcs, out_h, out_w, nullptr, nullptr,
              pl->P);
   TileShape ts;
-  const int tile = choose_tile(pl->P, out_h, out_w, (int)interp, o.tile, false);
-  make_geom(pl->P, out_h, out_w, (int)interp, tile, o, pl->G, ts);
+  LdsNeeds known;
+  const int tile = choose_tile(pl->P, out_h, out_w, (int)interp, o.tile, false, known);
+  make_geom(pl->P, out_h, out_w, (int)interp, tile, o, pl->G, ts, known);
   pl->np = ts.np;
   // A target with SIP has models unless they cannot be had now: no memory, or
   // `stream` under capture, where an allocation ends the capture and the prepass
@@ -680,10 +688,11 @@ dfr_status dfr_autotune(const float *src, int32_t src_h, int32_t src_w, int64_t 
   // the models do not depend on the tile: computed once, the tile kernels timed
   std::lock_guard<std::mutex> lk(workspace_mutex());
   if ((s = models_for(P, out_h, out_w, o, st)) != DFR_OK) return s;
+  LdsNeeds known;
   auto run = [&](int t) -> bool {
     TileGeom G;
     TileShape ts;
-    make_geom(P, out_h, out_w, (int)interp, t, o, G, ts);
+    make_geom(P, out_h, out_w, (int)interp, t, o, G, ts, known);
     return launch_forward_f32(P, G, (int)interp, ts.np, st) == hipSuccess;
   };
   int best = 0;
@@ -711,10 +720,11 @@ dfr_status dfr_autotune_batch(int32_t n, const dfr_frame *frames, const dfr_wcs 
   dfr_options o;
   resolve_options(opt, o);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  LdsNeeds known;
   auto run = [&](int t) -> bool {
     TileGeom Gt;
     int npt = 0;
-    batch_geom(plans, out_h, out_w, (int)interp, t, o, Gt, npt);
+    batch_geom(plans, out_h, out_w, (int)interp, t, o, Gt, npt, known);
     return run_batch(plans, Gt, (int)interp, npt, max_sord, o.precision == DFR_PREC_F32, st,
                      false) == DFR_OK;
   };

@@ -72,13 +72,18 @@ void save_cache_locked() {
   std::rename(tmp.c_str(), path);
 }
 
-int lds_need(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int tile) {
-  TileShape s;
-  tile_shape(tile, s);
-  return estimate_lds_floats(P, out_h, out_w, s, interp);
-}
-
 }  // namespace
+
+int lds_need(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int tile,
+             LdsNeeds &known) {
+  int &need = known.floats[tile];
+  if (need == 0) {
+    TileShape s;
+    tile_shape(tile, s);
+    need = estimate_lds_floats(P, out_h, out_w, s, interp);
+  }
+  return need;
+}
 
 std::string tune_key(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, bool batch) {
   double mag = max_magnification(P, out_h, out_w);
@@ -115,7 +120,7 @@ void tune_store(const std::string &key, int tile) {
 }
 
 int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int requested,
-                bool batch, int lds_factor, int pref, int64_t images) {
+                bool batch, LdsNeeds &known, int lds_factor, int pref, int64_t images) {
   if (requested >= 1 && requested <= kTileCount) return requested;
   {
     std::lock_guard<std::mutex> lk(g_tune_mutex);
@@ -136,8 +141,8 @@ int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, in
     TileShape a, b;
     tile_shape(pref, a);
     tile_shape(kDefaultTile, b);
-    const double na = lds_need(P, out_h, out_w, interp, pref);
-    const double nb = lds_need(P, out_h, out_w, interp, kDefaultTile);
+    const double na = lds_need(P, out_h, out_w, interp, pref, known);
+    const double nb = lds_need(P, out_h, out_w, interp, kDefaultTile, known);
     // the flat 128x16 tile gives way to 64x64 where that one's box is at most
     // 0.7 of its own per output pixel: a map turned by 3 degrees or more, or by
     // 90, where the flat tile's box is tall and its rows short (6000x4000
@@ -146,7 +151,7 @@ int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, in
     if (pref == kFlatTile) {
       TileShape c;
       tile_shape(kSquareTile, c);
-      const double nc = lds_need(P, out_h, out_w, interp, kSquareTile);
+      const double nc = lds_need(P, out_h, out_w, interp, kSquareTile, known);
       if (lds_factor * nc <= kLdsMaxFloats &&
           nc / (c.width * c.height) <= 0.7 * na / (a.width * a.height))
         return kSquareTile;
@@ -155,12 +160,12 @@ int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, in
         na / (a.width * a.height) <= 1.5 * nb / (b.width * b.height))
       return pref;
   }
-  const double nb = lds_need(P, out_h, out_w, interp, kDefaultTile);
+  const double nb = lds_need(P, out_h, out_w, interp, kDefaultTile, known);
   if (lds_factor * nb <= kLdsMaxFloats) {
     TileShape b, c;
     tile_shape(kDefaultTile, b);
     tile_shape(kSquareTile, c);
-    const double nc = lds_need(P, out_h, out_w, interp, kSquareTile);
+    const double nc = lds_need(P, out_h, out_w, interp, kSquareTile, known);
     if (lds_factor * nc <= kLdsMaxFloats &&
         nc / (c.width * c.height) <= 0.95 * nb / (b.width * b.height))
       return kSquareTile;
@@ -168,12 +173,12 @@ int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, in
   }
   const int order[] = {4, 8, 1, 7, 10};
   for (int t : order)
-    if (lds_factor * lds_need(P, out_h, out_w, interp, t) <= kLdsMaxFloats) return t;
+    if (lds_factor * lds_need(P, out_h, out_w, interp, t, known) <= kLdsMaxFloats) return t;
   return 7;
 }
 
 void make_geom(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int tile,
-               const dfr_options &o, TileGeom &G, TileShape &ts, int lds_factor) {
+               const dfr_options &o, TileGeom &G, TileShape &ts, LdsNeeds &known, int lds_factor) {
   tile_shape(tile, ts);
   std::memset(&G, 0, sizeof(G));
   G.out_h = out_h;
@@ -182,7 +187,7 @@ void make_geom(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int
   G.tiles_x = (out_w + ts.width - 1) / ts.width;
   int64_t ty = (out_h + ts.height - 1) / ts.height;
   G.n_tiles = (int32_t)(G.tiles_x * ty);
-  int64_t need = (int64_t)lds_factor * estimate_lds_floats(P, out_h, out_w, ts, interp);
+  int64_t need = (int64_t)lds_factor * lds_need(P, out_h, out_w, interp, tile, known);
   G.lds_cap = need <= kLdsMaxFloats ? (int32_t)need : 0;
   G.cubic_a = (float)o.cubic_a;
   G.nan_outside = o.nan_outside ? 1 : 0;
@@ -256,12 +261,13 @@ void single_setup(const float *src, int32_t src_h, int32_t src_w, int64_t src_pi
     std::memset(&G, 0, sizeof(G));
     std::memset(&ts, 0, sizeof(ts));
     if (out_h > 0 && out_w > 0) {
-      int tile = choose_tile(P, out_h, out_w, interp, o.tile, false, lds_factor, pref);
+      LdsNeeds known;
+      int tile = choose_tile(P, out_h, out_w, interp, o.tile, false, known, lds_factor, pref);
       TileShape t4;
       if (two_rows && tile_shape(tile, t4) && t4.np == 4) tile -= 1;
       dfr_options base;
       dfr_options_init(&base);
-      make_geom(P, out_h, out_w, interp, tile, base, G, ts, lds_factor);
+      make_geom(P, out_h, out_w, interp, tile, base, G, ts, known, lds_factor);
     }
     std::lock_guard<std::mutex> lk(g_setup_mutex);
     if (g_setup.size() >= kSetupCacheMax) g_setup.clear();

@@ -14,12 +14,22 @@ namespace dfr {
 
 constexpr int kLdsMaxFloats = 16384;  // 64 KiB of LDS per work-group for staged source
 
+// The LDS estimates made so far for one frame, output and interpolation, by tile
+// (0: not yet).  One costs about 10 us of the host's time, and the choice of a
+// tile and its geometry ask for some of them more than once.
+struct LdsNeeds {
+  int floats[kTileCount + 1] = {};
+};
+int lds_need(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int tile,
+             LdsNeeds &known);
+
 // Tile for a reprojection: `requested` if nonzero, else the tuned cache
 // entry for this kind of map, else a heuristic that fits the LDS budget.
 // pref: the untuned shape to try first (0: the forward's default for the
 // interpolation and `images` outputs of that size).
 int choose_tile(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int requested,
-                bool batch, int lds_factor = 1, int pref = 0, int64_t images = 1);
+                bool batch, LdsNeeds &known, int lds_factor = 1, int pref = 0,
+                int64_t images = 1);
 
 // Key under which tuned tiles are cached: kind, interpolation, SIP order and
 // coarse classes of the map's magnification and rotation.
@@ -46,7 +56,8 @@ void single_setup(const float *src, int32_t src_h, int32_t src_w, int64_t src_pi
 
 // lds_factor: copies of the source box a kernel keeps (backward: 2).
 void make_geom(const FramePlan &P, int32_t out_h, int32_t out_w, int interp, int tile,
-               const dfr_options &o, TileGeom &G, TileShape &ts, int lds_factor = 1);
+               const dfr_options &o, TileGeom &G, TileShape &ts, LdsNeeds &known,
+               int lds_factor = 1);
 
 // Scratch owned by the library for one (device, stream): device memory for
 // partial sums and the batch frame table, pinned staging for the frame table,

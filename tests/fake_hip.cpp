@@ -3,12 +3,34 @@
 // failed call leaves its error until hipGetLastError takes it; a call that
 // succeeds does not clear it).  Loaded before libdfr.so, its symbols are the
 // ones the library binds to.
+#include <dlfcn.h>
+
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <string>
 
+// The library's own estimate of a tile's LDS (a symbol it exports, so that this
+// one takes its place): counted, then made by the library.
+static int g_estimates = 0;
+static void *g_library = nullptr;
+namespace dfr {
+struct FramePlan;
+struct TileShape;
+int estimate_lds_floats(const FramePlan &P, int32_t h, int32_t w, const TileShape &s, int interp) {
+  using Fn = int (*)(const FramePlan &, int32_t, int32_t, const TileShape &, int);
+  static const Fn real = reinterpret_cast<Fn>(
+      dlsym(g_library, "_ZN3dfr19estimate_lds_floatsERKNS_9FramePlanEiiRKNS_9TileShapeEi"));
+  ++g_estimates;
+  return real(P, h, w, s, interp);
+}
+}  // namespace dfr
+
 extern "C" {
+
+void fake_set_library(const char *path) { g_library = dlopen(path, RTLD_LAZY | RTLD_NOLOAD); }
+int fake_estimates() { return g_estimates; }
 
 typedef int hipError_t;
 struct dim3_ {

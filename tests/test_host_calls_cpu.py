@@ -21,6 +21,7 @@ sys.modules["torch"] = None
 spec = importlib.util.spec_from_file_location("_lib", sys.argv[2])
 lib = importlib.util.module_from_spec(spec)
 spec.loader.exec_module(lib)
+fake.fake_set_library(lib.LIB_PATH.encode())
 
 keep = []
 
@@ -215,4 +216,28 @@ for k in [3] * 6 + [40] * 6 + [3] * 3 + [40]:
     assert stack("coadd", k) == OK
     asked.append(fake.fake_host_mallocs())
 assert asked == [1] * 6 + [2] * 10, asked
+''')
+
+
+def test_new_geometry_estimates_each_tile_once(fake):
+    """The set-up of a geometry not met before asks for the LDS of up to three
+    tile shapes, each estimated once, whichever default tile applies; a stack
+    adds one estimate per further frame."""
+    run(fake, '''
+def estimates(f):
+    before = fake.fake_estimates()
+    assert f() == OK
+    return fake.fake_estimates() - before
+counts = {}
+for interp in (0, 1, 2):
+    for out in (64, 2048, 4000, 6001):
+        for rot in (0.1, 5.0, 45.0, 90.0):
+            one = lambda: lib.dfr_reproject(IMG, 64, 64, 64, wcs(rot, 0, 2), wcs(0.0, 0, 0, out), out, out,
+                                            interp, IMG, IMG, opts(), STREAM)
+            counts[interp, out, rot] = estimates(one)
+            assert estimates(one) == 0
+print(counts)
+assert all(1 <= c <= 3 for c in counts.values())
+assert estimates(lambda: stack("batch", 3, out=6001)) <= 3 + 2
+assert estimates(lambda: stack("coadd", 3)) == 3
 ''')
