@@ -180,6 +180,12 @@ def _check(status: int, where: str):
         raise DfrError(status, where)
 
 
+def _plain(t: torch.Tensor) -> torch.Tensor:
+    """``t`` without its tensor subclass, which what is made from it with
+    ``new_empty`` would inherit: results are plain tensors."""
+    return t if type(t) is torch.Tensor else t.as_subclass(torch.Tensor)
+
+
 def _src_tensor(src) -> torch.Tensor:
     if not isinstance(src, torch.Tensor):
         src = torch.as_tensor(np.ascontiguousarray(src, dtype=np.float32))
@@ -191,7 +197,7 @@ def _src_tensor(src) -> torch.Tensor:
         raise ValueError("source image must be 2-D [rows, cols]")
     if src.stride(1) != 1:
         src = src.contiguous()
-    return src
+    return _plain(src)
 
 
 def reproject(src, src_wcs, tgt_wcs, shape_out=None, order="bilinear", *, footprint=True,
@@ -518,7 +524,7 @@ def sq_residual(out, ref, mask=None, want_grad=True):
     out = out.contiguous()
     ref = ref.contiguous()
     n = out.numel()
-    loss = out.new_empty(1, dtype=torch.float64)
+    loss = _plain(out).new_empty(1, dtype=torch.float64)
     g = torch.empty_like(out) if want_grad else None
     m = mask.contiguous().float() if mask is not None else None
     s = _lib.dfr_sq_residual(out.data_ptr(), ref.data_ptr(), _ptr(m), n, loss.data_ptr(),

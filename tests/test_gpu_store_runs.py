@@ -51,3 +51,25 @@ def test_window_at_any_column(dfr, x0, w):
                                                boxes=[[x0, 3, w, 70]])
     assert torch.equal(outs[0], full[3:73, x0:x0 + w])
     assert torch.equal(fps[0], full_fp[3:73, x0:x0 + w])
+
+
+class Tagged(torch.Tensor):
+    pass
+
+
+def test_results_of_a_tensor_subclass_are_plain(dfr):
+    """Outputs, footprints, gradients and the loss are made by the library:
+    they do not take on the subclass of the source."""
+    c = configs.grad(size=96)
+    src = torch.from_numpy(c.src).cuda()
+    args = (c.src_wcs, c.tgt_wcs, c.out_shape, "bilinear")
+    want, _ = dfr.reproject(src, *args)
+    for s in (src.as_subclass(Tagged), torch.nn.Parameter(src.clone())):
+        out, fp = dfr.reproject(s, *args)
+        loss, _ = dfr.sq_residual(out.as_subclass(Tagged), want)
+        gs, gw = dfr.reproject_backward(s, *args, torch.ones(c.out_shape, device="cuda"))
+        with dfr.Plan(src.shape, *args) as plan:
+            po, pf = plan.execute(s)
+        for t in (out, fp, loss, gs, gw, po, pf):
+            assert type(t) is torch.Tensor and not t.requires_grad
+        assert torch.equal(out, want) and torch.equal(po, want) and float(loss) == 0.0
