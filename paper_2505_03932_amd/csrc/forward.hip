@@ -16,7 +16,8 @@ static TileKernel pick_tile_kernel(int interp, int np, int sord) {
 }
 
 bool forward_small(const FramePlan &P, const TileGeom &G, int np) {
-  return np == 1 && G.n_tiles <= kSmallTiles && P.t_order == 0 && P.s_order <= 5;
+  const int most = P.s_order == 5 ? kSmallTilesOrder5 : kSmallTiles;
+  return np == 1 && G.n_tiles <= most && P.t_order == 0 && P.s_order <= 5;
 }
 
 hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int interp,

@@ -85,8 +85,15 @@ hipError_t launch_forward_f32(const FramePlan &P, const TileGeom &G, int interp,
                               hipStream_t stream);
 // Whether a call with cell models takes the one-launch form for few tiles
 // (launch_forward_small, no model table): tiles of one row per thread, up to
-// the groups that run at once beside the FP64 registers.
+// the groups that run at once beside the FP64 registers: three per CU and 768
+// where the instance takes at most 170 of them (orders 0 to 4), two and 512 at
+// order 5 (182 to 184).  Above, a second round of groups pays the models' chain
+// again.  us per call at order 5, nearest, bilinear, bicubic: one launch at 704^2
+// (484 groups) 13.7, 10.9, 13.2; at 768^2 (576) 16.8, 13.4, 16.5 and with the
+// table 14.4, 13.1, 13.5.  At order 4 one launch at 864^2 (729) 12.2, 11.0, 13.6,
+// the table at 880^2 (784) 13.7, 13.0, 13.8.
 constexpr int kSmallTiles = 768;
+constexpr int kSmallTilesOrder5 = 512;
 bool forward_small(const FramePlan &P, const TileGeom &G, int np);
 hipError_t launch_forward_small(const FramePlan &P, const TileGeom &G, int interp,
                                 hipStream_t stream);

@@ -25,7 +25,8 @@ void reproject_tiles(FramePlan P, TileGeom G) {
 }
 
 // The same with each group making the models of its own cells (32x32 and
-// 64x16 tiles: one or two of them), for outputs of few tiles: one launch and no
+// 64x16 tiles: one or two of them; 128x8 and 256x4, where they are asked for: four
+// and eight, a lane each), for outputs of few tiles: one launch and no
 // table.  The FP64 chain is then on every group's path, but while the groups
 // are few they all run at once, so it costs its own latency (about 2 us) in
 // place of a launch that waits for another one (256x256 bilinear: 15.2 us per

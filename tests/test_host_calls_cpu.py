@@ -241,3 +241,14 @@ assert all(1 <= c <= 3 for c in counts.values())
 assert estimates(lambda: stack("batch", 3, out=6001)) <= 3 + 2
 assert estimates(lambda: stack("coadd", 3)) == 3
 ''')
+
+
+@pytest.mark.parametrize("order,most", [(0, 768), (3, 768), (4, 768), (5, 512)])
+def test_one_launch_form_up_to_the_groups_that_run_at_once(fake, order, most):
+    run(fake, f'''
+def launched(rows):
+    s = lib.dfr_reproject(IMG, 64, 64, 64, wcs(0.3, 0, {order}), wcs(), 32 * rows, 32, 1, IMG, IMG, opts(), STREAM)
+    assert s == OK
+    return names()[-1]
+assert "reproject_small" in launched({most}) and "reproject_small" not in launched({most} + 1)
+''')
