@@ -108,3 +108,19 @@ def test_captured_without_a_workspace(dfr):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want) and torch.equal(fp, want_fp)
+
+
+def test_cropped_windows_take_the_same_models(dfr):
+    c = configs.sip3(scale=0.06)
+    tw = _target(c.tgt_wcs, 3, 50.0, 180.0)
+    src = torch.from_numpy(c.src).cuda()
+    h, w = c.out_shape
+    for interp in ("nearest", "bilinear", "bicubic"):
+        print(f"cropped target sip interp={interp}", flush=True)
+        o, f = dfr.reproject(src, c.src_wcs, tw, (h, w), interp)
+        boxes = [[0, 0, w, h], [33, 17, w - 61, h - 40], [5, 5, 1, 1]]
+        outs, fps, _ = dfr.reproject_batch_cropped([src] * 3, [c.src_wcs] * 3, tw, (h, w), interp,
+                                                   boxes=boxes)
+        for (x, y, bw, bh), oc, fc in zip(boxes, outs, fps):
+            assert torch.equal(oc, o[y:y + bh, x:x + bw]) and torch.equal(fc, f[y:y + bh, x:x + bw])
+        assert dfr.batch_boxes([src], [c.src_wcs], tw, (h, w), interp).tolist() == [[0, 0, w, h]]
