@@ -327,7 +327,6 @@ struct TileBox {
   bool use_lds;            // staged (fits the LDS budget)
   bool interior;           // no per-pixel checks needed
   bool all_model;          // every cell has a certified model
-  bool touch;              // some cell can reach the source
 };
 
 template <int NP>
@@ -349,7 +348,6 @@ __device__ __forceinline__ TileBox tile_box(const FramePlan &P, const TileGeom &
   B.interior = B.use_lds && sh.cells_ok && (P.t_order == 0 || sh.all_model) && bu0 == B.bi0 && bu1 == B.bi1 &&
                bu2 == B.bj0 && bu3 == B.bj1 && T.x0 + T.TW <= G.out_w && T.y0 + T.TH <= G.out_h;
   B.all_model = sh.all_model;
-  B.touch = sh.touch;
   return B;
 }
 
