@@ -500,15 +500,21 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
   w->staging.pending[slot] = true;
   const int lds_bytes = G.lds_cap * (int)sizeof(float);
   int4 *parts = boxes ? reinterpret_cast<int4 *>(dev + pofs) : nullptr;
-  const dim3 mgrid((unsigned)n * (unsigned)bpf);
   const void *mkernel = cell_models_batch_ptr(msord, tord);
-  void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev, &parts};
   const void *parts_in = parts;
   void *rargs[] = {&plans_dev, &parts_in, &bpf};
   if (!graph) {
-    if ((run.reach_host ? boxes : models) &&
-        launch_kernel(mkernel, mgrid, dim3(64), margs, 0, stream) != hipSuccess)
-      return DFR_E_DEVICE;
+    // (a launch has fewer than 2^32 threads: whole frames, as many as that allows)
+    const int step = std::max(1, ((1 << 26) - 1) / bpf);
+    for (int f = 0; f < n && (run.reach_host ? boxes : models); f += step) {
+      const FramePlan *plans_f = plans_dev + f;
+      CellModel *models_f = models_dev ? models_dev + f * ncells : nullptr;
+      int4 *parts_f = parts ? parts + (int64_t)f * bpf : nullptr;
+      void *args[] = {&plans_f, &ncx_i, &ncy_i, &bcols, &bpf, &models_f, &parts_f};
+      if (launch_kernel(mkernel, dim3((unsigned)std::min(step, n - f) * (unsigned)bpf), dim3(64),
+                        args, 0, stream) != hipSuccess)
+        return DFR_E_DEVICE;
+    }
     if (boxes &&
         launch_kernel(reach_kernel_ptr(), dim3(n), dim3(256), rargs, 0, stream) != hipSuccess)
       return DFR_E_DEVICE;
@@ -550,11 +556,13 @@ dfr_status run_batch(const std::vector<FramePlan> &plans, const TileGeom &G, int
       if (hipGraphCreate(&bg.graph, 0) != hipSuccess) return DFR_E_DEVICE;
       hipGraphNode_t mod = nullptr, box = nullptr, kern = nullptr;
       bool ok = true;
+      void *margs[] = {&plans_dev, &ncx_i, &ncy_i, &bcols, &bpf, &models_dev, &parts};
       if (models) {
         hipKernelNodeParams mp;
         std::memset(&mp, 0, sizeof(mp));
         mp.func = const_cast<void *>(mkernel);
-        mp.gridDim = mgrid;
+        // (kBatchItems bounds the cells of a graph's frames far below a launch's limit)
+        mp.gridDim = dim3((unsigned)n * (unsigned)bpf);
         mp.blockDim = dim3(64);
         mp.kernelParams = margs;
         ok = hipGraphAddKernelNode(&mod, bg.graph, nullptr, 0, &mp) == hipSuccess;

@@ -82,7 +82,7 @@ hipError_t hipMalloc(void **p, size_t n) {
     --g_fail_malloc;
     return done(2);
   }
-  *p = std::malloc(n);
+  *p = std::malloc(n < (256u << 20) ? n : 256u << 20);  // (only its first part is written here)
   return 0;
 }
 hipError_t hipFree(void *p) {
@@ -129,7 +129,8 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
   *p = scratch;
   return 0;
 }
-hipError_t hipLaunchKernel(const void *f, dim3_, dim3_, void **, size_t, void *) {
+hipError_t hipLaunchKernel(const void *f, dim3_ grid, dim3_ block, void **, size_t, void *) {
+  if (grid.x * (uint64_t)block.x > 0xffffffffull) return done(9);  // the limit of a launch
   if (g_skip_launches > 0) {
     --g_skip_launches;
   } else if (g_fail_launch > 0) {

@@ -252,3 +252,17 @@ def launched(rows):
     return names()[-1]
 assert "reproject_small" in launched({most}) and "reproject_small" not in launched({most} + 1)
 ''')
+
+
+def test_prepass_of_many_cells_takes_several_launches(fake):
+    """A launch has fewer than 2^32 threads; the prepass rounds a strip one cell
+    high up to blocks of 8x8 cells, so 2100 frames on one of 262144 cells reach
+    that long before the memory of their models ends."""
+    run(fake, '''
+def coadd(k):
+    return lib.dfr_coadd_batch(k, frames(k), wcs(), 32, 1 << 23, 1, IMG, IMG, None, 0, opts(), STREAM)
+assert coadd(2000) == OK
+assert ["cell_models_batch" in n for n in names()].count(True) == 1
+assert coadd(2100) == OK
+assert ["cell_models_batch" in n for n in names()].count(True) == 3
+''')
