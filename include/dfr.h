@@ -134,8 +134,9 @@ dfr_status dfr_reproject(const float *src, int32_t src_h, int32_t src_w, int64_t
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * call as dfr_reproject, same arguments, same kernels and bit-identical
- * results, but it allocates nothing.  The per-cell model table that
+ * call as dfr_reproject, same arguments, and, except for a target with SIP
+ * (below), the same kernels and bit-identical results, but it allocates
+ * nothing.  The per-cell model table that
  * dfr_reproject keeps in a per-stream workspace lives instead in a fixed
  * device array of DFR_NOALLOC_SCRATCH_BYTES (8 MiB) that every GPU the
  * library runs on holds until the process ends.

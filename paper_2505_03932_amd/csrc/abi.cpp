@@ -778,7 +778,8 @@ dfr_status dfr_cell_model(const dfr_wcs *src_wcs, const dfr_wcs *tgt_wcs, int32_
   build_plan(nullptr, 0, 0, 0, *src_wcs, *tgt_wcs, (cy + 1) * kCell, (cx + 1) * kCell, nullptr,
              nullptr, P);
   CellModel M;
-  cell_model<-1>(P, SipCoefs{P.sA, P.sB, P.tA, P.tB}, cx, cy, M);  // (the models of a target with SIP exist on the device only)
+  // (a target with SIP gets none here: its models are made on the device only)
+  cell_model<-1>(P, SipCoefs{P.sA, P.sB, P.tA, P.tB}, cx, cy, M);
   for (int k = 0; k < 10; ++k) {
     if (coef_x) coef_x[k] = M.mx[k];
     if (coef_y) coef_y[k] = M.my[k];

@@ -50,3 +50,15 @@ def test_same_bits_as_a_plan(dfr, order, interp):
     q = dfr.reproject(src, sw, tw, (300, 301), interp, precision="f32_anchor", debug_positions=True)[2]
     if interp != "nearest":
         assert (p - q).abs().nan_to_num().max().item() <= 2e-5
+
+
+@pytest.mark.parametrize("interp", ["nearest", "bilinear", "bicubic"])
+def test_order_5_around_its_own_limit(dfr, interp):
+    s, sw, tw = _case(5)
+    src = torch.from_numpy(s).cuda()
+    for shape in [(511 * 32, 32), (16 * 32, 32 * 32), (513 * 32, 32)]:  # 511, 512 and 513 tiles
+        print(f"small order 5 interp={interp} shape={shape}", flush=True)
+        o, f = dfr.reproject(src, sw, tw, shape, interp)
+        with dfr.Plan(src.shape, sw, tw, shape, interp) as plan:
+            po, pf = plan.execute(src)
+        assert torch.equal(o, po) and torch.equal(f, pf) and f.any()
